@@ -15,13 +15,15 @@
 //                         rows, K split over the 4 wavefronts (private
 //                         direct-to-LDS rings), bf16 MFMAs into fp32, the four
 //                         partials added in wavefront order, bf16 out;
-//   linear_bf16_tiled_kernel  the same result for many rows, from 128 x 128
-//                         or 128 x 192 output tiles (W read once per 128 rows);
+//   linear_bf16_tiled_kernel  the same result for many rows, from 128 x 128,
+//                         128 x 192 or 256 x 192 output tiles;
 //   rope_scatter_kernel   rotate-half RoPE of the Q and K heads from fp32 cos /
 //                         sin tables, V unrotated, scattered to each row's
 //                         position in Q, K, V.
 // Token ids outside [0, vocab) and row indices outside [0, N) are skipped on
 // the device (no access is made for them).
+#include <type_traits>
+
 #include "device.h"
 #include "launch.h"
 
@@ -29,6 +31,12 @@ namespace lacache {
 namespace {
 
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+// two fp32 -> bf16, nearest-even, in one instruction
+__device__ __forceinline__ uint32_t cvt_pk_bf16(float lo, float hi) {
+  const bf2 v = {static_cast<__bf16>(lo), static_cast<__bf16>(hi)};
+  return __builtin_bit_cast(uint32_t, v);
+}
 
 template <int T>
 __global__ __launch_bounds__(256) void embed_rmsnorm_kernel(const int32_t* __restrict__ ids,
@@ -209,140 +217,203 @@ __global__ __launch_bounds__(kLinSplit * 64) void linear_bf16_kernel(const uint1
     float sum = red[row * NC + col];
 #pragma unroll
     for (int wv = 1; wv < kLinSplit; ++wv) sum += red[(wv * RA + row) * NC + col];
-    out[(m0 + row) * N + n0 + col] = static_cast<uint16_t>(f32_to_bf16(sum));
+    out[(m0 + row) * N + n0 + col] = static_cast<uint16_t>(cvt_pk_bf16(sum, 0.0f));
     if (out_tap != nullptr) out_tap[(m0 + row) * N + n0 + col] = sum;
   }
 }
 
 // out = a W^T for many rows: BM x BN output tiles, 8 wavefronts (4 bands of
-// BM/4 activation rows x 2 bands of BN/2 weight rows), one direct-to-LDS ring
-// of 3 stages shared by the workgroup (K-steps of 64 elements: BM activation
-// rows and BN weight rows a stage), so a staged activation row serves BN
-// weight rows and a staged weight row BM activation rows; with BM = 128, W
-// is read once per 128 rows instead of once per 64. Every output element gets exactly the
-// arithmetic of linear_bf16_kernel: the same four K quarters, each a chain of
-// the same 16x16x32 bf16 MFMAs on the same operand halves (K-step by K-step)
-// started from zero, and the quarter sums added in quarter order. So a row's
-// result does not depend on which of the two kernels computed it, and a
-// block update of the caches still equals a full recompute bit for bit.
-constexpr int kLtWaves = 8, kLtS = 3;
+// BM/4 activation rows x 2 bands of BN/2 weight rows), walked by a grid of at
+// most one workgroup per CU in the XCD-grouped order (the row tiles that share
+// a weight tile run on one L2). A K-step is 64 elements (128 bytes of a row:
+// 64-byte row pieces would halve the rate at which a CU copies from L2, 65
+// against 120-130 GB/s measured with 256 CUs copying). Wavefronts 0-3 copy the
+// activation rows, wavefronts 4-7 the weight rows; separate wavefronts and
+// rings, because a wavefront's copies retire in order and the weights, which
+// come from HBM, need the deeper ring where the LDS does not hold both deep. Every output element gets exactly the arithmetic of
+// linear_bf16_kernel: the same four K quarters, each a chain of the same
+// 16x16x32 bf16 MFMAs in K order started from zero, and the quarter sums added
+// in quarter order (the total starts from +0, which adds exactly: a chain that
+// starts from +0 never ends in -0). So a row's result does not depend on which
+// of the two kernels computed it, and a block update of the caches still
+// equals a full recompute bit for bit.
+//
+// LDS operand reads bound the 128-row tiles: a wavefront reads MT + NT slabs
+// (1 KB each) for MT NT MFMAs of 16 cycles, and the LDS gives 128 bytes per
+// cycle, so half a K-step of 8 wavefronts needs 64 (MT + NT) LDS cycles beside
+// 32 MT NT cycles of MFMA work per SIMD: 640 against 768 at 256 x 192, but 512
+// against 384 at 128 x 192. The two accumulator sets of the 256 x 192 tile (192
+// registers) leave no room to read a half step's operands ahead, so there the
+// two wavefronts of a SIMD alternate (kPing): one reads its operands and
+// issues copies while the other multiplies, a barrier between the phases.
+constexpr int kLtWaves = 8;
 #ifndef LACACHE_LIN_TILED_MIN_M
 #define LACACHE_LIN_TILED_MIN_M 128
 #endif
 constexpr int64_t kLinTiledMinM = LACACHE_LIN_TILED_MIN_M;  // rows above which the tiled kernel runs
 
-// BM x BN output tile; wavefront (wm, wn) of 4 x 2 owns BM/4 rows x BN/2
-// columns (MT x NT 16x16 tiles)
-template <int BM, int BN>
+template <int BM, int BN, bool kPing>
 __global__ __launch_bounds__(kLtWaves * 64) void linear_bf16_tiled_kernel(const uint16_t* __restrict__ a,
                                                                         const uint16_t* __restrict__ w,
                                                                         uint16_t* __restrict__ out,
                                                                         float* __restrict__ out_tap, int64_t M,
-                                                                        int64_t N, int64_t K) {
-  constexpr int kStage = (BM + BN) * 128;             // bytes per stage
-  constexpr int kPer = (BM + BN) / 8 / kLtWaves;      // 1 KB copies per wavefront per stage
-  constexpr int MT = BM / 64, NT = BN / 32, WRr = BM / 4, WCc = BN / 2;
-  static_assert((BM + BN) % (8 * kLtWaves) == 0 && BM % 64 == 0 && BN % 32 == 0, "tile shape");
-  __shared__ __align__(16) uint8_t ring[kLtS][kStage];
+                                                                        int64_t N, int64_t K, int R, int C) {
+  constexpr int kA = BM * 128, kB = BN * 128;  // bytes of a K-step's activation and weight rows
+  // steps in the two rings (a power of two of activations): 4 and 4, or 2 and 4 at 256 x 192
+  constexpr int DA = 4 * (kA + kB) <= 163840 ? 4 : 2;
+  constexpr int DB = (163840 - DA * kA) / kB > 4 ? 4 : (163840 - DA * kA) / kB;
+  constexpr int MT = BM / 64, NT = BN / 32;
+  constexpr int PA = BM / 32, PB = BN / 32;  // copies per step of an activation / a weight copy wavefront
+  constexpr int PM = PA > PB ? PA : PB;
+  static_assert(BM % 64 == 0 && BN % 32 == 0 && DB >= 3, "tile shape");
+  __shared__ __align__(16) uint8_t sA[DA][kA];
+  __shared__ __align__(16) uint8_t sB[DB][kB];
   const int t = threadIdx.x, lane = t & 63;
   const int wave = wave_uniform(t >> 6);
   const int q = lane >> 4, lr = lane & 15;
   const int wm = wave >> 1, wn = wave & 1;
-  // row tiles along x (up to 2^24 / 128 of them; gridDim.y is limited to
-  // 65536), column tiles along y
-  const int64_t m0 = static_cast<int64_t>(blockIdx.x) * BM;
-  const int64_t n0 = static_cast<int64_t>(blockIdx.y) * BN;
+  const bool late = wave >= 4;  // copies weights; with kPing half a phase behind the others
   const int KS = static_cast<int>(K / 64);
-  const uint8_t* ab = reinterpret_cast<const uint8_t*>(a);
-  const uint8_t* wb = reinterpret_cast<const uint8_t*>(w);
+  const uint32_t K2 = static_cast<uint32_t>(K) * 2u;
+  // copy plan: copy u of wavefront v fills tile rows 8 g .. 8 g + 7, g = v % 4
+  // + 4 u; lane l fills row l/8, physical chunk l%8, i.e. logical chunk (l%8) ^
+  // ((row/2) mod 8), which spreads the 16 rows of an operand read over all banks
+  const int crow = lane >> 3;
+  const uint32_t cchunk = static_cast<uint32_t>(((lane & 7) ^ (4 * (wave & 1) + (crow >> 1))) << 4);
+  const uint32_t coff = static_cast<uint32_t>(8 * (wave & 3) + crow) * K2;
+  // this lane's operand bytes of a 16-row slab, first and second half of the K-step
+  const int frag[2] = {lr * 128 + ((q ^ (lr >> 1)) << 4), lr * 128 + (((4 + q) ^ (lr >> 1)) << 4)};
 
-  // copy plan: copy u of wavefront v fills stage rows 8 g .. 8 g + 7, g = v + 8 u
-  // (rows 0..BM-1 activations, then BN weight rows); lane l fills row 8 g + l/8,
-  // physical chunk l%8, i.e. logical chunk (l%8) ^ (row & 7)
-  const int crow = lane >> 3, pch = lane & 7;
-  int64_t src[kPer];
+  for (int item = blockIdx.x; item < R * C; item += gridDim.x) {
+    int rt, ct;
+    xcd_grouped_tile(item, R, C, rt, ct);
+    const int64_t m0 = static_cast<int64_t>(rt) * BM, n0 = static_cast<int64_t>(ct) * BN;
+    // rows past M fetch the last row; their results are never stored
+    const uint8_t* base = late ? reinterpret_cast<const uint8_t*>(w + n0 * K) : reinterpret_cast<const uint8_t*>(a + m0 * K);
+    const int64_t last = late ? BN - 1 : (M - 1 - m0 < BM - 1 ? M - 1 - m0 : BM - 1);
+    const uint32_t lim = static_cast<uint32_t>(last) * K2;
+    auto issue = [&](int ks, uint8_t* dst, auto count) {
+      constexpr int P = decltype(count)::value;
+      const int lds = static_cast<int>(lds_u32(dst)) + (wave & 3) * 1024;
+      // past the end the last step is copied again into an idle stage (never read)
+      const uint8_t* g = base + static_cast<int64_t>(ks < KS ? ks : KS - 1) * 128;
 #pragma unroll
-  for (int u = 0; u < kPer; ++u) {
-    const int row = 8 * (wave + kLtWaves * u) + crow;
-    const int chunk = (pch ^ (row & 7)) << 4;
-    if (row < BM) {
-      const int64_t gr = m0 + row < M ? m0 + row : M - 1;
-      src[u] = gr * K * 2 + chunk;
-    } else {
-      src[u] = (n0 + row - BM) * K * 2 + chunk;
-    }
-  }
-  auto issue = [&](int ks, int st) {
-    const uint32_t base = lds_u32(&ring[st][0]);
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const int g = wave + kLtWaves * u;
-      const uint8_t* b = (8 * g < BM ? ab : wb) + src[u] + static_cast<int64_t>(ks) * 128;
-      dma16(b, wave_uniform(static_cast<int>(base) + g * 1024));
-    }
-  };
-
-  v4f acc[MT][NT], tot[MT][NT];
-  const v4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-  for (int i = 0; i < MT; ++i)
-#pragma unroll
-    for (int j = 0; j < NT; ++j) tot[i][j] = zero;
-#pragma unroll
-  for (int s = 0; s < kLtS - 1; ++s)
-    if (s < KS) issue(s, s);
-  int ks = 0;
-  for (int qq = 0; qq < kLinSplit; ++qq) {
-    const int k1 = (qq + 1) * KS / kLinSplit;
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-      for (int j = 0; j < NT; ++j) acc[i][j] = zero;
-    for (; ks < k1; ++ks) {
-      // this wavefront's copies of step ks have landed (later ones may fly) ...
-      if (ks + kLtS - 2 < KS)
-        wait_vm<(kLtS - 2) * kPer>();
-      else
-        wait_vm<0>();
-      bar();  // ... and every wavefront's; the stage refilled next is read by no one
-      if (ks + kLtS - 1 < KS) issue(ks + kLtS - 1, (ks + kLtS - 1) % kLtS);
-      const uint8_t* st = &ring[ks % kLtS][0];
-      bf8 alo[MT], ahi[MT];
-#pragma unroll
-      for (int i = 0; i < MT; ++i) lin_frag(st + (WRr * wm + 16 * i) * 128, lr, q, alo[i], ahi[i]);
-#pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        bf8 blo, bhi;
-        lin_frag(st + (BM + WCc * wn + 16 * j) * 128, lr, q, blo, bhi);
-#pragma unroll
-        for (int i = 0; i < MT; ++i) {
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(alo[i], blo, acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ahi[i], bhi, acc[i][j], 0, 0, 0);
-        }
+      for (int u = 0; u < P; ++u) {
+        const uint32_t o = coff + static_cast<uint32_t>(32 * u) * K2;
+        dma16s(g, (o < lim ? o : lim) + cchunk, wave_uniform(lds + u * 4096));
       }
-    }
-    // the quarter's sum joins the total in quarter order (the first is a copy)
+    };
+    auto issue_a = [&](int ks) { issue(ks, &sA[ks & (DA - 1)][0], std::integral_constant<int, PA>{}); };
+    auto issue_b = [&](int ks, int slot) { issue(ks, &sB[slot][0], std::integral_constant<int, PB>{}); };
+    // this wavefront's copies of the next step to be read have landed
+    auto landed = [&]() {
+      if (late)
+        wait_vm<(DB - 2) * PB>();
+      else
+        wait_vm<(DA - 2) * PA>();
+    };
+
+    v4f acc[MT][NT], tot[MT][NT];
+    const v4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) tot[i][j] = zero;
+    if (late) {
+#pragma unroll
+      for (int s = 0; s < DB - 1; ++s) issue_b(s, s);
+    } else {
+#pragma unroll
+      for (int s = 0; s < DA - 1; ++s) issue_a(s);
+    }
+    if (kPing) {
+      landed();
+      bar();  // K-step 0 is in LDS
+      if (late) bar();
+    }
+    int ks = 0, cur = 0;
+    for (int qq = 0; qq < kLinSplit; ++qq) {
+      const int k1 = (qq + 1) * KS / kLinSplit;
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = zero;
+      for (; ks < k1; ++ks) {
+        auto refill = [&]() {  // into the stages of step ks - 1, which every wavefront has read
+          if (late)
+            issue_b(ks + DB - 1, cur == 0 ? DB - 1 : cur - 1);
+          else
+            issue_a(ks + DA - 1);
+        };
+        if (!kPing) {
+          landed();
+          bar();  // ... and every wavefront's copies; the stages refilled next are read by no one
+          refill();
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const uint8_t* pa = &sA[ks & (DA - 1)][0] + frag[h] + MT * wm * 2048;
+          const uint8_t* pb = &sB[cur][0] + frag[h] + NT * wn * 2048;
+          bf8 af[MT], bf[NT];
+#pragma unroll
+          for (int i = 0; i < MT; ++i) af[i] = *reinterpret_cast<const bf8*>(pa + i * 2048);
+#pragma unroll
+          for (int j = 0; j < NT; ++j) bf[j] = *reinterpret_cast<const bf8*>(pb + j * 2048);
+          if (kPing) {
+            if (h == 0) refill();
+            if (h == 1 && late) landed();
+            wait_lds();
+            bar();
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_setprio(1);
+          }
+          // weight rows first: a lane's four results are four consecutive columns of one row
+#pragma unroll
+          for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[j], af[i], acc[i][j], 0, 0, 0);
+          if (kPing) {
+            __builtin_amdgcn_s_setprio(0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (h == 1 && !late) landed();
+            bar();
+          }
+        }
+        cur = cur + 1 == DB ? 0 : cur + 1;
+      }
+      // the quarter's sum joins the total in quarter order
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) tot[i][j][r] = tot[i][j][r] + acc[i][j][r];
+    }
+    if (kPing && !late) bar();
+    wait_vm<0>();  // the trailing repeat copies
+    bar();         // every wavefront is done with the ring: the next item may refill it
+    const int64_t col0 = n0 + 16 * NT * wn + 4 * q;
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      const int64_t row = m0 + 16 * (MT * wm + i) + lr;
+      if (row >= M) continue;
+      uint16_t* o = out + row * N + col0;
 #pragma unroll
       for (int j = 0; j < NT; ++j)
+        *reinterpret_cast<uint2*>(o + 16 * j) =
+            make_uint2(cvt_pk_bf16(tot[i][j][0], tot[i][j][1]), cvt_pk_bf16(tot[i][j][2], tot[i][j][3]));
+    }
+    if (out_tap != nullptr) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) tot[i][j][r] = qq == 0 ? acc[i][j][r] : tot[i][j][r] + acc[i][j][r];
-  }
-  wait_vm<0>();
+      for (int i = 0; i < MT; ++i) {
+        const int64_t row = m0 + 16 * (MT * wm + i) + lr;
+        if (row >= M) continue;
 #pragma unroll
-  for (int i = 0; i < MT; ++i)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t row = m0 + WRr * wm + 16 * i + 4 * q + r;
-      if (row >= M) continue;
-#pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        const int64_t col = n0 + WCc * wn + 16 * j + lr;
-        out[row * N + col] = static_cast<uint16_t>(f32_to_bf16(tot[i][j][r]));
-        if (out_tap != nullptr) out_tap[row * N + col] = tot[i][j][r];
+        for (int j = 0; j < NT; ++j) *reinterpret_cast<v4f*>(out_tap + row * N + col0 + 16 * j) = tot[i][j];
       }
     }
+  }
 }
 
 // One thread per (row r, Q/K/V part, head, pair i < 64): the pair (i, i + 64)
@@ -398,20 +469,29 @@ hipError_t launch_embed_rmsnorm(hipStream_t st, const int32_t* ids, const int32_
 hipError_t launch_linear_bf16(hipStream_t st, const uint16_t* a, const uint16_t* w, uint16_t* out, float* out_tap,
                               int64_t M, int64_t N, int64_t K) {
   if (M > kLinTiledMinM) {
-    // many rows: 128-row tiles (N % 128 == 0), W read once per 128 rows
-    // 128 x 192 tiles when they need fewer rounds of one workgroup per CU
-    // than 128 x 128 (measured at N = 12288, K = 4096: 52 against 72 us at
-    // M = 512, 122 against 132 us at M = 1024; at M = 256, with one round
-    // either way, 128 x 128 leaves fewer CUs idle: 39 against 47 us)
-    const int64_t rt = (M + 127) / 128, cus = device_cu_count();
-    const bool wide = N % 192 == 0 && (rt * (N / 192) + cus - 1) / cus < (rt * (N / 128) + cus - 1) / cus;
-    const dim3 block(kLtWaves * 64);
-    if (wide)
-      hipLaunchKernelGGL((linear_bf16_tiled_kernel<128, 192>), dim3(static_cast<unsigned>(rt), static_cast<unsigned>(N / 192)),
-                         block, 0, st, a, w, out, out_tap, M, N, K);
+    // The tile with the least rounds x cost, the cost of a round in units of a
+    // 128 x 128 one as measured at N = 12288, K = 4096 (one round: 43 us at
+    // 128 x 128, 57 at 128 x 192, 84 at 256 x 192): M = 256 runs in 43 us, 512 in
+    // 60, 768 in 80 and 1000 in 91 (113 and 119 with 128-row tiles alone)
+    const int64_t cus = device_cu_count();
+    auto cost = [&](int64_t bm, int64_t bn, int64_t unit) {
+      return N % bn != 0 ? INT64_MAX : (((M + bm - 1) / bm) * (N / bn) + cus - 1) / cus * unit;
+    };
+    const int64_t c0 = cost(128, 128, 20), c1 = cost(128, 192, 27), c2 = cost(256, 192, 39);
+#define LT(BM_, BN_, PING_)                                                                                       \
+  do {                                                                                                           \
+    const int r_ = static_cast<int>((M + BM_ - 1) / BM_), c_ = static_cast<int>(N / BN_);                        \
+    hipLaunchKernelGGL((linear_bf16_tiled_kernel<BM_, BN_, PING_>),                                              \
+                       dim3(static_cast<unsigned>(static_cast<int64_t>(r_) * c_ < cus ? r_ * c_ : cus)),         \
+                       dim3(kLtWaves * 64), 0, st, a, w, out, out_tap, M, N, K, r_, c_);                         \
+  } while (0)
+    if (c2 < c0 && c2 < c1)
+      LT(256, 192, true);
+    else if (c1 < c0)
+      LT(128, 192, false);
     else
-      hipLaunchKernelGGL((linear_bf16_tiled_kernel<128, 128>), dim3(static_cast<unsigned>(rt), static_cast<unsigned>(N / 128)),
-                         block, 0, st, a, w, out, out_tap, M, N, K);
+      LT(128, 128, false);
+#undef LT
     return hipGetLastError();
   }
   // up to 64 rows per pass; the last pass may hold fewer slabs. Three weight

@@ -136,6 +136,32 @@ def test_linear_tiled_equals_streaming(M, N, K):
         _linear_check(a, w, out, tap)
 
 
+@pytest.mark.parametrize("M,K", [(769, 128), (769, 384), (1000, 640)])
+def test_linear_256_row_tiles_equal_streaming(M, K):
+    """256 x 192 tiles (the choice at N = 12288 above 512 rows): a last row
+    tile of one valid row, K quarters that are empty (K = 128) or of unequal
+    length (K = 384, 640), byte for byte the streaming kernel's result."""
+    N = 12288
+    rng = np.random.default_rng(M + K)
+    a = to_bf16_bits(rng.standard_normal((M, K)).astype(np.float32))
+    w = to_bf16_bits((0.03 * rng.standard_normal((N, K))).astype(np.float32))
+    da, dw = dev_bf16(a), dev_bf16(w)
+    _say("256-row tiles M=%d K=%d" % (M, K))
+    out = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
+    tap = torch.full((M, N), float("nan"), dtype=torch.float32, device=DEV)
+    lc.lacache_linear_bf16(da, dw, out, tap)
+    rows = [0, 255, 256, 511, 512, 767, 768, M - 1]
+    out_s = torch.empty((len(rows), N), dtype=torch.bfloat16, device=DEV)
+    tap_s = torch.empty((len(rows), N), dtype=torch.float32, device=DEV)
+    ri = torch.tensor(rows, device=DEV)
+    lc.lacache_linear_bf16(da.index_select(0, ri).contiguous(), dw, out_s, tap_s)
+    torch.cuda.synchronize()
+    assert torch.isfinite(tap).all().item()
+    assert torch.equal(tap.index_select(0, ri).view(torch.int32), tap_s.view(torch.int32))
+    assert torch.equal(out.index_select(0, ri).view(torch.int16), out_s.view(torch.int16))
+    _linear_check(a[rows], w, out_s, tap_s)
+
+
 def test_linear_maximum_m():
     """M = 2^24 rows, the most the library takes (131072 row tiles): every row
     written, and sampled rows equal to the streaming kernel's bytes and within
