@@ -620,11 +620,9 @@ int lacache_first_layer_tokens(void* stream, const int32_t* token_ids, const int
   void* base = nullptr;
   RETURN_IF(get_workspace(static_cast<hipStream_t>(stream), lacache_first_layer_workspace_bytes(R, heads, H), &base));
   uint16_t* y = static_cast<uint16_t*>(base);
-  uint16_t* qkv = reinterpret_cast<uint16_t*>(static_cast<char*>(base) + align256(static_cast<size_t>(R * H) * 2));
   hipStream_t st = static_cast<hipStream_t>(stream);
   RETURN_IF(hip_status(launch_embed_rmsnorm(st, token_ids, rows, R, embed, vocab, norm_w, embed_cache, N, y, H)));
-  RETURN_IF(hip_status(launch_linear_bf16(st, y, w_qkv, qkv, nullptr, R, static_cast<int64_t>(nq), H)));
-  return hip_status(launch_rope_scatter(st, qkv, rows, R, rope_cos, rope_sin, q, k, v, heads, N));
+  return hip_status(launch_linear_rope(st, y, w_qkv, rows, R, rope_cos, rope_sin, q, k, v, heads, N, H));
 }
 
 int lacache_add_bf16(void* stream, uint16_t* x_inout, const uint16_t* y, int64_t n) {

@@ -99,6 +99,29 @@ __global__ __launch_bounds__(256) void embed_rmsnorm_kernel(const int32_t* __res
   }
 }
 
+// The RoPE + scatter of rope_scatter_kernel as the epilogue of the two
+// projection kernels below (kRope; W is then w_qkv, N = 3 heads 128): the
+// projection's rows are rounded to bf16, rotated and written to their places
+// in q, k, v, and never go through memory. A tile's columns are then not
+// consecutive: a pair (i, i + 64) of a head meets in one wavefront, so the
+// tile takes P consecutive pairs of the 64 3 heads (pair p: head p / 64, i =
+// p mod 64) and weight rows i and i + 64 for each. Rows whose position is
+// outside [0, N) write nothing.
+struct RopeArgs {
+  const int32_t* rows;
+  const float* cs;
+  const float* sn;
+  uint16_t* q;
+  uint16_t* k;
+  uint16_t* v;
+  int heads;
+  int64_t N;
+};
+__device__ __forceinline__ uint16_t* rope_dst(const RopeArgs& ra, int head) {
+  const int part = head / ra.heads;
+  return (part == 0 ? ra.q : (part == 1 ? ra.k : ra.v)) + static_cast<int64_t>(head - part * ra.heads) * ra.N * 128;
+}
+
 // out [M x N] = a [M x K] W[N x K]^T, bf16 in and out, fp32 accumulation.
 // Workgroup (blockIdx.x, blockIdx.y): weight rows 16 NJ x .. (NJ slabs of
 // 16), activation rows 64 y .. + 63 (MT slabs of 16 rows). Its 4 wavefronts
@@ -128,12 +151,14 @@ __device__ __forceinline__ void lin_frag(const uint8_t* rows, int lr, int q, bf8
   hi = *reinterpret_cast<const bf8*>(row + (((4 + q) ^ (lr & 7)) << 4));
 }
 
-template <int MT, int NJ>
+//
+// kRope: a slab is 8 pairs, rows i .. i + 7 of a head and then i + 64 .. i + 71.
+template <int MT, int NJ, bool kRope>
 __global__ __launch_bounds__(kLinSplit * 64) void linear_bf16_kernel(const uint16_t* __restrict__ a,
                                                                      const uint16_t* __restrict__ w,
                                                                      uint16_t* __restrict__ out,
                                                                      float* __restrict__ out_tap, int64_t M,
-                                                                     int64_t N, int64_t K) {
+                                                                     int64_t N, int64_t K, RopeArgs ra) {
   using C = LinCfg<MT, NJ>;
   constexpr int D = C::D, RA = C::RA, NC = 16 * NJ;
   __shared__ __align__(16) uint8_t ring[kLinSplit][D * C::kSlot];
@@ -163,7 +188,12 @@ __global__ __launch_bounds__(kLinSplit * 64) void linear_bf16_kernel(const uint1
 #pragma unroll
   for (int u = 0; u < 2 * NJ; ++u) {
     const int row = 8 * u + crow;
-    w_off[u] = (n0 + row) * K * 2 + ((pch ^ (row & 7)) << 4);
+    int64_t wrow = n0 + row;
+    if (kRope) {  // 8 pairs of slab u / 2, the lower rows (u even) or the upper
+      const int64_t p0 = n0 / 2 + 8 * (u >> 1);
+      wrow = (p0 >> 6) * 128 + (p0 & 63) + 64 * (u & 1) + crow;
+    }
+    w_off[u] = wrow * K * 2 + ((pch ^ (row & 7)) << 4);
   }
   auto issue = [&](int s, int slot) {
     const int64_t kb = (ks0 + (s < nks ? s : nks - 1)) * 128;  // byte offset of the K-step
@@ -211,6 +241,31 @@ __global__ __launch_bounds__(kLinSplit * 64) void linear_bf16_kernel(const uint1
 #pragma unroll
       for (int r = 0; r < 4; ++r) red[(wave * RA + 16 * i + 4 * q + r) * NC + 16 * j + lr] = acc[i][j][r];
   __syncthreads();
+  if (kRope) {
+    for (int e = t; e < RA * (NC / 2); e += kLinSplit * 64) {
+      const int row = e / (NC / 2), p = e - row * (NC / 2);
+      if (m0 + row >= M) continue;
+      const int64_t pos = ra.rows[m0 + row];
+      if (pos < 0 || pos >= ra.N) continue;
+      const int lo = row * NC + 16 * (p >> 3) + (p & 7);  // the pair's upper row is 8 columns on
+      float x = red[lo], y = red[lo + 8];
+#pragma unroll
+      for (int wv = 1; wv < kLinSplit; ++wv) {
+        x += red[wv * RA * NC + lo];
+        y += red[wv * RA * NC + lo + 8];
+      }
+      const int pair = static_cast<int>(n0 / 2) + p, head = pair >> 6, i = pair & 63;
+      uint16_t* dst = rope_dst(ra, head) + pos * 128 + i;
+      uint32_t xy = cvt_pk_bf16(x, y);
+      if (head < 2 * ra.heads) {
+        const float c = ra.cs[pos * 64 + i], s = ra.sn[pos * 64 + i], xb = bf16lo(xy), yb = bf16hi(xy);
+        xy = cvt_pk_bf16(xb * c - yb * s, yb * c + xb * s);
+      }
+      dst[0] = static_cast<uint16_t>(xy);
+      dst[64] = static_cast<uint16_t>(xy >> 16);
+    }
+    return;
+  }
   for (int e = t; e < RA * NC; e += kLinSplit * 64) {
     const int row = e / NC, col = e - row * NC;
     if (m0 + row >= M) continue;
@@ -252,12 +307,15 @@ constexpr int kLtWaves = 8;
 #endif
 constexpr int64_t kLinTiledMinM = LACACHE_LIN_TILED_MIN_M;  // rows above which the tiled kernel runs
 
-template <int BM, int BN, bool kPing>
+// kRope: a wavefront's NT slabs are NT/2 slabs of 16 pairs' lower rows, then
+// the same pairs' upper rows (weight rows 64 on).
+template <int BM, int BN, bool kPing, bool kRope>
 __global__ __launch_bounds__(kLtWaves * 64) void linear_bf16_tiled_kernel(const uint16_t* __restrict__ a,
                                                                         const uint16_t* __restrict__ w,
                                                                         uint16_t* __restrict__ out,
                                                                         float* __restrict__ out_tap, int64_t M,
-                                                                        int64_t N, int64_t K, int R, int C) {
+                                                                        int64_t N, int64_t K, int R, int C,
+                                                                        RopeArgs ra) {
   constexpr int kA = BM * 128, kB = BN * 128;  // bytes of a K-step's activation and weight rows
   // steps in the two rings (a power of two of activations): 4 and 4, or 2 and 4 at 256 x 192
   constexpr int DA = 4 * (kA + kB) <= 163840 ? 4 : 2;
@@ -289,9 +347,22 @@ __global__ __launch_bounds__(kLtWaves * 64) void linear_bf16_tiled_kernel(const 
     xcd_grouped_tile(item, R, C, rt, ct);
     const int64_t m0 = static_cast<int64_t>(rt) * BM, n0 = static_cast<int64_t>(ct) * BN;
     // rows past M fetch the last row; their results are never stored
-    const uint8_t* base = late ? reinterpret_cast<const uint8_t*>(w + n0 * K) : reinterpret_cast<const uint8_t*>(a + m0 * K);
+    const uint8_t* base = late ? reinterpret_cast<const uint8_t*>(kRope ? w : w + n0 * K)
+                               : reinterpret_cast<const uint8_t*>(a + m0 * K);
     const int64_t last = late ? BN - 1 : (M - 1 - m0 < BM - 1 ? M - 1 - m0 : BM - 1);
-    const uint32_t lim = static_cast<uint32_t>(last) * K2;
+    const uint32_t lim = late && kRope ? 0xFFFFFFFFu : static_cast<uint32_t>(last) * K2;
+    // byte offset of copy u's 8 rows from the first copy's (kRope: weight rows
+    // by pair slab; below 2^32, as N K < 2^31)
+    uint32_t uoff[kRope ? PM : 1];
+    if (kRope) {
+#pragma unroll
+      for (int u = 0; u < PM; ++u) {
+        const int g = (wave & 3) + 4 * u, slab = g >> 1, j = slab % NT;
+        const int ps = ct * (BN / 32) + (slab / NT) * (NT / 2) + j % (NT / 2);
+        const int row = (ps >> 2) * 128 + (ps & 3) * 16 + (j < NT / 2 ? 0 : 64) + 8 * (g & 1);
+        uoff[u] = late ? static_cast<uint32_t>(row - 8 * (wave & 3)) * K2 : static_cast<uint32_t>(32 * u) * K2;
+      }
+    }
     auto issue = [&](int ks, uint8_t* dst, auto count) {
       constexpr int P = decltype(count)::value;
       const int lds = static_cast<int>(lds_u32(dst)) + (wave & 3) * 1024;
@@ -299,7 +370,7 @@ __global__ __launch_bounds__(kLtWaves * 64) void linear_bf16_tiled_kernel(const 
       const uint8_t* g = base + static_cast<int64_t>(ks < KS ? ks : KS - 1) * 128;
 #pragma unroll
       for (int u = 0; u < P; ++u) {
-        const uint32_t o = coff + static_cast<uint32_t>(32 * u) * K2;
+        const uint32_t o = coff + (kRope ? uoff[kRope ? u : 0] : static_cast<uint32_t>(32 * u) * K2);
         dma16s(g, (o < lim ? o : lim) + cchunk, wave_uniform(lds + u * 4096));
       }
     };
@@ -393,6 +464,35 @@ __global__ __launch_bounds__(kLtWaves * 64) void linear_bf16_tiled_kernel(const 
     if (kPing && !late) bar();
     wait_vm<0>();  // the trailing repeat copies
     bar();         // every wavefront is done with the ring: the next item may refill it
+    if (kRope) {
+#pragma unroll
+      for (int i = 0; i < MT; ++i) {
+        const int64_t row = m0 + 16 * (MT * wm + i) + lr;
+        const int64_t pos = row < M ? ra.rows[row] : -1;
+        if (pos < 0 || pos >= ra.N) continue;
+#pragma unroll
+        for (int j = 0; j < NT / 2; ++j) {
+          const int ps = ct * (BN / 32) + wn * (NT / 2) + j, head = ps >> 2, i0 = (ps & 3) * 16 + 4 * q;
+          uint16_t* dst = rope_dst(ra, head) + pos * 128 + i0;
+          const v4f x = tot[i][j], y = tot[i][j + NT / 2];
+          uint32_t lo[2] = {cvt_pk_bf16(x[0], x[1]), cvt_pk_bf16(x[2], x[3])};
+          uint32_t hi[2] = {cvt_pk_bf16(y[0], y[1]), cvt_pk_bf16(y[2], y[3])};
+          if (head < 2 * ra.heads) {
+            const v4f c = *reinterpret_cast<const v4f*>(ra.cs + pos * 64 + i0);
+            const v4f s = *reinterpret_cast<const v4f*>(ra.sn + pos * 64 + i0);
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+              const float x0 = bf16lo(lo[e]), x1 = bf16hi(lo[e]), y0 = bf16lo(hi[e]), y1 = bf16hi(hi[e]);
+              lo[e] = cvt_pk_bf16(x0 * c[2 * e] - y0 * s[2 * e], x1 * c[2 * e + 1] - y1 * s[2 * e + 1]);
+              hi[e] = cvt_pk_bf16(y0 * c[2 * e] + x0 * s[2 * e], y1 * c[2 * e + 1] + x1 * s[2 * e + 1]);
+            }
+          }
+          *reinterpret_cast<uint2*>(dst) = make_uint2(lo[0], lo[1]);
+          *reinterpret_cast<uint2*>(dst + 64) = make_uint2(hi[0], hi[1]);
+        }
+      }
+      continue;  // the next item
+    }
     const int64_t col0 = n0 + 16 * NT * wn + 4 * q;
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
@@ -466,8 +566,11 @@ hipError_t launch_embed_rmsnorm(hipStream_t st, const int32_t* ids, const int32_
   return hipGetLastError();
 }
 
-hipError_t launch_linear_bf16(hipStream_t st, const uint16_t* a, const uint16_t* w, uint16_t* out, float* out_tap,
-                              int64_t M, int64_t N, int64_t K) {
+namespace {
+
+template <bool kRope>
+hipError_t launch_linear(hipStream_t st, const uint16_t* a, const uint16_t* w, uint16_t* out, float* out_tap, int64_t M,
+                         int64_t N, int64_t K, const RopeArgs& ra) {
   if (M > kLinTiledMinM) {
     // The tile with the least rounds x cost, the cost of a round in units of a
     // 128 x 128 one as measured at N = 12288, K = 4096 (one round: 43 us at
@@ -481,9 +584,9 @@ hipError_t launch_linear_bf16(hipStream_t st, const uint16_t* a, const uint16_t*
 #define LT(BM_, BN_, PING_)                                                                                       \
   do {                                                                                                           \
     const int r_ = static_cast<int>((M + BM_ - 1) / BM_), c_ = static_cast<int>(N / BN_);                        \
-    hipLaunchKernelGGL((linear_bf16_tiled_kernel<BM_, BN_, PING_>),                                              \
+    hipLaunchKernelGGL((linear_bf16_tiled_kernel<BM_, BN_, PING_, kRope>),                                              \
                        dim3(static_cast<unsigned>(static_cast<int64_t>(r_) * c_ < cus ? r_ * c_ : cus)),         \
-                       dim3(kLtWaves * 64), 0, st, a, w, out, out_tap, M, N, K, r_, c_);                         \
+                       dim3(kLtWaves * 64), 0, st, a, w, out, out_tap, M, N, K, r_, c_, ra);                         \
   } while (0)
     if (c2 < c0 && c2 < c1)
       LT(256, 192, true);
@@ -501,7 +604,7 @@ hipError_t launch_linear_bf16(hipStream_t st, const uint16_t* a, const uint16_t*
   const int mt = static_cast<int>(M >= 64 ? 4 : (M + 15) / 16);
   const bool wide = mt <= 2 && N % 48 == 0 && N / 48 >= 256;
   const dim3 grid(static_cast<unsigned>(N / (wide ? 48 : 16)), passes), block(kLinSplit * 64);
-#define LB(MT_, NJ_) hipLaunchKernelGGL((linear_bf16_kernel<MT_, NJ_>), grid, block, 0, st, a, w, out, out_tap, M, N, K)
+#define LB(MT_, NJ_) hipLaunchKernelGGL((linear_bf16_kernel<MT_, NJ_, kRope>), grid, block, 0, st, a, w, out, out_tap, M, N, K, ra)
   if (wide) {
     if (mt <= 1) LB(1, 3);
     else LB(2, 3);
@@ -511,6 +614,20 @@ hipError_t launch_linear_bf16(hipStream_t st, const uint16_t* a, const uint16_t*
   else LB(4, 1);
 #undef LB
   return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_linear_bf16(hipStream_t st, const uint16_t* a, const uint16_t* w, uint16_t* out, float* out_tap,
+                              int64_t M, int64_t N, int64_t K) {
+  return launch_linear<false>(st, a, w, out, out_tap, M, N, K, RopeArgs{});
+}
+
+hipError_t launch_linear_rope(hipStream_t st, const uint16_t* y, const uint16_t* w_qkv, const int32_t* rows, int64_t R,
+                              const float* cs, const float* sn, uint16_t* q, uint16_t* k, uint16_t* v, int64_t heads,
+                              int64_t N, int64_t H) {
+  return launch_linear<true>(st, y, w_qkv, nullptr, nullptr, R, 3 * heads * 128, H,
+                             RopeArgs{rows, cs, sn, q, k, v, static_cast<int>(heads), N});
 }
 
 hipError_t launch_rope_scatter(hipStream_t st, const uint16_t* qkv, const int32_t* rows, int64_t R, const float* cs,

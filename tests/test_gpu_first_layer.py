@@ -259,3 +259,31 @@ def test_block_update_equals_full_recompute(H, heads, N):
             blk = g[:, (part * heads + h) * D:(part * heads + h + 1) * D]
             ref = blk if part == 2 else F.rope(blk, C, cos_t, sin_t)
             assert np.array_equal(got[h, C], ref)
+
+
+@pytest.mark.parametrize("R,heads,H", [(1, 1, 128), (9, 32, 256), (33, 3, 256), (100, 2, 384), (300, 1, 128),
+                                       (300, 32, 128), (1000, 32, 256)])
+def test_fused_rope_epilogue_equals_the_stages(R, heads, H):
+    """RoPE and scatter in the projection's epilogue, on every projection
+    kernel (one and three weight slabs, one to four activation slabs, two
+    passes; the three tile shapes), byte for byte the three stage calls', with
+    rows in any order and some positions outside the sequence (skipped)."""
+    N, vocab = R + 7, 200
+    rng, embed, nw, wqkv, cos_t, sin_t = _setup(H, heads, N, vocab, seed=R + heads)
+    ids = rng.integers(0, vocab, R)
+    rows = rng.permutation(N)[:R]
+    if R > 2:
+        rows[R // 2], rows[0] = N, -1
+    _say("fused rope R=%d heads=%d H=%d" % (R, heads, H))
+    fused, staged = _caches(heads, N, H), _caches(heads, N, H)
+    _full_call(ids, rows, embed, nw, wqkv, cos_t, sin_t, fused)
+    y = torch.zeros((R, H), dtype=torch.bfloat16, device=DEV)
+    qkv = torch.empty((R, 3 * heads * D), dtype=torch.bfloat16, device=DEV)
+    lc.lacache_embed_rmsnorm(_i32(ids), _i32(rows), dev_bf16(embed), dev_bf16(nw), staged[0], y)
+    lc.lacache_linear_bf16(y, dev_bf16(wqkv), qkv)
+    lc.lacache_rope_scatter(qkv, _i32(rows), torch.from_numpy(cos_t).to(DEV), torch.from_numpy(sin_t).to(DEV),
+                            *staged[1:])
+    torch.cuda.synchronize()
+    for a, b in zip(fused, staged):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+    assert not torch.isnan(fused[1][:, rows[-1]].float()).any()
