@@ -2,17 +2,19 @@
 //   gate/up: x[M x H] . Wgu[2I x H]^T, fused SwiGLU and 1x128 re-quantization
 //   down:    h[M x I] . Wd[H x I]^T -> bf16
 //
-// Work items are BM-row x 256-weight-row output tiles (times the K splits of
-// the down GEMM). The grid is persistent: one workgroup per CU walks the items
+// Work items are BM-row x BNR-weight-row output tiles (BM 64 to 256 by the
+// rules at the launchers; BNR 256, or 128 for the down GEMM's smaller tiles),
+// times the K splits of the down GEMM. The grid is persistent: one workgroup per CU walks the items
 // b, b + G, b + 2G, ... (G workgroups), and its copy ring runs straight across
 // item boundaries, so the first K-groups of the next tile are already in LDS
 // when a tile's epilogue ends and no workgroup launch or pipeline refill
 // separates two tiles.
 //
-// A workgroup has 8 wavefronts; wavefront (wm, wn) owns 64 activation rows x
-// WC weight rows (4 x NJ sub-tiles of 16 x 16). K is walked one 128-wide group
+// A workgroup has 8 multiplying wavefronts (four of them also copy, or up to 128-row
+// tiles four more only copy); wavefront (wm, wn) owns WR activation rows x
+// WC weight rows (MT x NJ sub-tiles of 16 x 16). K is walked one 128-wide group
 // at a time:
-//   * the group's fp8 tiles (A: BM x 128 B, B: 256 x 128 B), the BM
+//   * the group's fp8 tiles (A: BM x 128 B, B: BNR x 128 B), the BM
 //     activation scales and the tile's two weight-block scales go global ->
 //     LDS with direct-to-LDS copies into a ring of stages, issued S - 1 groups
 //     ahead, so no registers hold staging data;
@@ -40,8 +42,6 @@
 namespace lacache {
 namespace {
 
-constexpr int BNR = 256;  // weight rows per tile
-
 // LDS tiles are [rows][128 bytes]; the eight 16-byte chunks of a row are
 // permuted by an xor with (row / 2) mod 8, which spreads the 16 rows of an
 // MFMA operand read over the banks.
@@ -60,13 +60,14 @@ __device__ __forceinline__ v8i load_frag(const uint8_t* tile, int row, int q) {
 }
 
 // One LDS stage: A tile, B tile, BM activation scales, the two weight-block
-// scales of the K-group (slots BM and BM + 1 of a 64-slot region written by
+// scales of the K-group (slots XR and XR + 1 of a 64-slot region written by
 // one copy instruction), and 64 spare slots for duplicate scale copies.
-template <int BM>
+template <int BM, int BNR>
 struct Stage {
+  static constexpr int XR = (BM + 63) / 64 * 64;  // activation scale slots (64 per copy instruction)
   uint8_t a[BM * 128];
   uint8_t b[BNR * 128];
-  alignas(16) float xs[BM + 128];
+  alignas(16) float xs[XR + 128];
 };
 
 // A work item: output tile (row tile, column tile) and its K range.
@@ -103,23 +104,34 @@ __device__ __forceinline__ Item item_at(int w, int R, int C, int KS, int KB, int
 
 }  // namespace
 
-constexpr int kTileWaves = 8;
+constexpr int kTileWaves = 8;  // wavefronts that multiply
+constexpr int kCopyWaves = 4;  // wavefronts that copy (one per SIMD)
+// Up to 128-row tiles the copies have wavefronts of their own (12 in all, at
+// most 168 VGPRs each), so no multiplying wavefront waits for the memory
+// pipeline to take its copies (H = 4096, I = 12288: down at 128 rows 20.9 ->
+// 18.8 us, gate/up at 192 rows 32.9 -> 31.8); taller tiles need the registers.
+constexpr bool tile_dedicated(int bm) { return bm <= 128; }
+constexpr int tile_threads(int bm) { return (kTileWaves + (tile_dedicated(bm) ? kCopyWaves : 0)) * 64; }
 
-template <bool kGateUp, int BM>
-__global__ __launch_bounds__(kTileWaves * 64) void gemm_tiled_kernel(
+template <bool kGateUp, int BM, int BNR>
+__global__ __launch_bounds__(tile_threads(BM)) void gemm_tiled_kernel(
     const uint8_t* __restrict__ aq, const float* __restrict__ as,  // [M x K] codes, [K/128 x M] scales
     const uint8_t* __restrict__ bq, const float* __restrict__ bs,  // [N x K] codes, [N/128 x K/128] scales
     uint8_t* __restrict__ hq, float* __restrict__ hs, float* __restrict__ h_tap,
     uint16_t* __restrict__ out, float* __restrict__ out_tap, float* __restrict__ part,
     const float* __restrict__ col_s, int64_t M, int64_t K, int64_t N, int64_t I, int KS, int W) {
-  static_assert(BM == 128 || BM == 256, "BM must be 128 or 256");
-  constexpr int NW = kTileWaves;
-  constexpr int WC = BM == 256 ? 128 : 64;  // weight rows (output columns) per wavefront
-  constexpr int NCW = BNR / WC;             // wavefronts along the weight rows
-  constexpr int NJ = WC / 16;               // 16-wide column slabs per wavefront
-  // LDS ring: 3 stages for BM = 128 (3 x 49.9 KB), 2 for BM = 256 (2 x 66.8 KB)
-  constexpr int S = BM == 128 ? 3 : 2;
-  __shared__ Stage<BM> stg[S];
+  constexpr bool kDed = tile_dedicated(BM);
+  constexpr int NCW = BM > 128 ? 2 : 4;       // wavefronts along the weight rows
+  constexpr int WC = BNR / NCW;               // weight rows (output columns) per wavefront
+  constexpr int WR = BM * NCW / kTileWaves;   // activation rows per wavefront
+  constexpr int MT = WR / 16, NJ = WC / 16;   // its 16 x 16 sub-tiles
+  static_assert(MT * 16 * kTileWaves == BM * NCW && NJ * 16 * NCW == BNR && (!kGateUp || BNR == 256), "tile shape");
+  using Stg = Stage<BM, BNR>;
+  constexpr int XR = Stg::XR;
+  // LDS ring: as many stages as fit (2 at BM = 256, 3 at BM = 64..128 x 256, 6 at 64 x 128)
+  constexpr int kRoom = 163840 - NCW * BM * 4;
+  constexpr int S = kRoom / static_cast<int>(sizeof(Stg)) > 6 ? 6 : kRoom / static_cast<int>(sizeof(Stg));
+  __shared__ Stg stg[S];
   __shared__ float sRed[NCW][BM];
 
   const int t = threadIdx.x, lane = t & 63;
@@ -131,8 +143,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void gemm_tiled_kernel(
   const int R = static_cast<int>((M + BM - 1) / BM);
   const int C = static_cast<int>(kGateUp ? I / 128 : (N + BNR - 1) / BNR);
   const int G = static_cast<int>(gridDim.x);
-
-  constexpr int kCopyWaves = 4;
+  const int cw = kDed ? wave - kTileWaves : wave;  // copy wavefront index
 
   // The copy wavefronts and the others run the same stream as two instances
   // of one loop: only the copy wavefronts' instance holds the copy cursor
@@ -148,14 +159,14 @@ __global__ __launch_bounds__(kTileWaves * 64) void gemm_tiled_kernel(
     // fills slot l, i.e. row 8g + l/8, physical chunk l%8, so it fetches logical
     // chunk (l%8) ^ swz(row) of that row. Rows past M (or N) fetch a clamped
     // row; their results are never stored. Scales: each copy wavefront copies
-    // the activation scales of rows 64 (w mod BM/64) .. + 63 (one float per
+    // the activation scales of rows 64 (w mod XR/64) .. + 63 (one float per
     // lane; copies beyond the first go to the spare slots) and the two
     // weight-block scales (lane 0 the first block, the others the second).
     constexpr int kAInst = BM / 8 / kCopyWaves;  // per copy wavefront
     constexpr int kBInst = BNR / 8 / kCopyWaves;
     constexpr int kPer = kAInst + kBInst + 2;  // copies per copy wavefront per K-group
-    const int xband = wave % (BM / 64);
-    const int xs_dst = wave < BM / 64 ? wave * 64 : BM + 64;
+    const int xband = cw % (XR / 64);
+    const int xs_dst = cw < XR / 64 ? cw * 64 : XR + 64;
 
     // issue cursor: the item whose K-groups are being copied
     int iw = blockIdx.x, ikb = 0, ikb1 = 0;
@@ -174,7 +185,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void gemm_tiled_kernel(
       const int alim = static_cast<int>(M) - 1 - it.m0;  // last valid row of the tile
 #pragma unroll
       for (int u = 0; u < (kCopy ? kAInst : 0); ++u) {
-        const int row = (wave * kAInst + u) * 8 + (lane >> 3);
+        const int row = (cw * kAInst + u) * 8 + (lane >> 3);
         const int r = row < alim ? row : alim;
         a_off[u] = static_cast<uint32_t>(r) * static_cast<uint32_t>(K) + ((lane & 7) ^ swz(row)) * 16;
       }
@@ -188,7 +199,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void gemm_tiled_kernel(
       // same as row-major, the offsets within and the K-group step are not)
 #pragma unroll
       for (int u = 0; u < (kCopy ? kBInst : 0); ++u) {
-        const int row = (wave * kBInst + u) * 8 + (lane >> 3);
+        const int row = (cw * kBInst + u) * 8 + (lane >> 3);
         const int r = row < blim ? row : blim;
         b_off[u] = static_cast<uint32_t>(wtile_off(r, ((lane & 7) ^ swz(row)) * 16, K));
       }
@@ -204,24 +215,24 @@ __global__ __launch_bounds__(kTileWaves * 64) void gemm_tiled_kernel(
       }
     };
     // Copies of K-group kb of the cursor's item into stage dst (asynchronous).
-    auto issue_group = [&](int kb, Stage<BM>* dst) {
+    auto issue_group = [&](int kb, Stg* dst) {
       const int64_t ko = static_cast<int64_t>(kb) * 128;
       const int la = static_cast<int>(lds_u32(dst->a)), lb = static_cast<int>(lds_u32(dst->b));
 #pragma unroll
-      for (int u = 0; u < (kCopy ? kAInst : 0); ++u) dma16s(a_base + ko, a_off[u], wave_uniform(la + (wave * kAInst + u) * 1024));
+      for (int u = 0; u < (kCopy ? kAInst : 0); ++u) dma16s(a_base + ko, a_off[u], wave_uniform(la + (cw * kAInst + u) * 1024));
 #pragma unroll
       for (int u = 0; u < (kCopy ? kBInst : 0); ++u) {
-        const uint8_t* base = (kGateUp && (wave * kBInst + u) * 8 >= 128) ? b_base_hi : b_base;
-        dma16s(base + ko * 16, b_off[u], wave_uniform(lb + (wave * kBInst + u) * 1024));
+        const uint8_t* base = (kGateUp && (cw * kBInst + u) * 8 >= 128) ? b_base_hi : b_base;
+        dma16s(base + ko * 16, b_off[u], wave_uniform(lb + (cw * kBInst + u) * 1024));
       }
       const int lx = static_cast<int>(lds_u32(dst->xs));
       dma4s(x_base + static_cast<int64_t>(kb) * M, x_off, wave_uniform(lx + xs_dst * 4));
-      dma4s(bs + kb, w_off, wave_uniform(lx + BM * 4));
+      dma4s(bs + kb, w_off, wave_uniform(lx + XR * 4));
     };
     // The next K-group in the workgroup's sequence. Past the last one the last
     // group is copied again into the idle stage (never read), so every step
     // waits for the same count.
-    auto issue_next = [&](Stage<BM>* dst) {
+    auto issue_next = [&](Stg* dst) {
       issue_group(ikb < ikb1 ? ikb : ikb1 - 1, dst);
       if (ikb < ikb1 && ++ikb == ikb1 && iw + G < W) {
         iw += G;
@@ -229,10 +240,10 @@ __global__ __launch_bounds__(kTileWaves * 64) void gemm_tiled_kernel(
       }
     };
 
-    float acc[4][NJ][4];
+    float acc[MT][NJ][4];
 
     // Multiplies the K-group in stage cur into acc.
-    auto compute = [&](const Stage<BM>* cur) {
+    auto compute = [&](const Stg* cur) {
       auto brow = [&](int j) {
         return kGateUp ? (j < NJ / 2 ? (WC / 2) * wn + 16 * j : 128 + (WC / 2) * wn + 16 * (j - NJ / 2)) : WC * wn + 16 * j;
       };
@@ -244,27 +255,27 @@ __global__ __launch_bounds__(kTileWaves * 64) void gemm_tiled_kernel(
       v8i bb[2];
       bb[0] = load_frag(cur->b, brow(0) + lr, q);
       __builtin_amdgcn_sched_barrier(0);
-      float xv[4];
+      float xv[MT];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) xv[i] = cur->xs[64 * wm + 16 * i + lr];
-      // gate/up: slabs 0..NJ/2-1 are gate rows (block scale in slot BM), the
-      // rest the matching up rows (slot BM + 1); down: the wave's columns lie in
-      // one block, slot BM + (WC wn) / 128
-      const float w0 = cur->xs[BM + (kGateUp ? 0 : (WC * wn) / 128)];
-      const float w1 = cur->xs[BM + 1];
+      for (int i = 0; i < MT; ++i) xv[i] = cur->xs[WR * wm + 16 * i + lr];
+      // gate/up: slabs 0..NJ/2-1 are gate rows (block scale in slot XR), the
+      // rest the matching up rows (slot XR + 1); down: the wave's columns lie in
+      // one block, slot XR + (WC wn) / 128
+      const float w0 = cur->xs[XR + (kGateUp ? 0 : (WC * wn) / 128)];
+      const float w1 = cur->xs[XR + 1];
       __builtin_amdgcn_sched_barrier(0);
-      v8i af[4];
+      v8i af[MT];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) af[i] = load_frag(cur->a, 64 * wm + 16 * i + lr, q);
+      for (int i = 0; i < MT; ++i) af[i] = load_frag(cur->a, WR * wm + 16 * i + lr, q);
       __builtin_amdgcn_sched_barrier(0);
-      float sc[kGateUp ? 2 : 1][4];  // RN32(x_scale * w_scale) of this lane's row
-      // Software pipeline over the 4 NJ sub-tiles s = 4 j + i: MFMA s, then the
+      float sc[kGateUp ? 2 : 1][MT];  // RN32(x_scale * w_scale) of this lane's row
+      // Software pipeline over the MT NJ sub-tiles s = MT j + i: MFMA s, then the
       // scale FMAs of MFMA s - 2; the B operand of slab j + 1 is read while slab
       // j multiplies.
       v4f pr[3];
 #pragma unroll
-      for (int s = 0; s < 4 * NJ; ++s) {
-        const int j = s >> 2, i = s & 3;
+      for (int s = 0; s < MT * NJ; ++s) {
+        const int j = s / MT, i = s % MT;
         if (i == 0 && j < NJ - 1) bb[(j + 1) & 1] = load_frag(cur->b, brow(j + 1) + lr, q);
         const v4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
         pr[s % 3] = mfma_fp8_16x16x128(bb[j & 1], af[i], zero);
@@ -273,25 +284,25 @@ __global__ __launch_bounds__(kTileWaves * 64) void gemm_tiled_kernel(
         __builtin_amdgcn_sched_barrier(0);
         if (s == 1) {
 #pragma unroll
-          for (int i2 = 0; i2 < 4; ++i2) {
+          for (int i2 = 0; i2 < MT; ++i2) {
             sc[0][i2] = xv[i2] * w0;
             if (kGateUp) sc[kGateUp ? 1 : 0][i2] = xv[i2] * w1;
           }
         }
         if (s >= 2) {
-          const int ps = s - 2;
-          const int blk = (kGateUp && (ps >> 2) >= NJ / 2) ? 1 : 0;
+          const int ps = s - 2, pj = ps / MT, pi = ps % MT;
+          const int blk = (kGateUp && pj >= NJ / 2) ? 1 : 0;
 #pragma unroll
-          for (int r = 0; r < 4; ++r)
-            acc[ps & 3][ps >> 2][r] = __builtin_fmaf(pr[ps % 3][r], sc[blk][ps & 3], acc[ps & 3][ps >> 2][r]);
+          for (int r = 0; r < 4; ++r) acc[pi][pj][r] = __builtin_fmaf(pr[ps % 3][r], sc[blk][pi], acc[pi][pj][r]);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
 #pragma unroll
-      for (int ps = 4 * NJ - 2; ps < 4 * NJ; ++ps)
+      for (int ps = MT * NJ - 2; ps < MT * NJ; ++ps)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          acc[ps & 3][ps >> 2][r] = __builtin_fmaf(pr[ps % 3][r], sc[kGateUp ? 1 : 0][ps & 3], acc[ps & 3][ps >> 2][r]);
+          acc[ps % MT][ps / MT][r] =
+              __builtin_fmaf(pr[ps % 3][r], sc[kGateUp ? 1 : 0][ps % MT], acc[ps % MT][ps / MT][r]);
     };
 
     // ---- the stream: S - 1 K-groups ahead of the multiply, across items
@@ -305,7 +316,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void gemm_tiled_kernel(
     for (int w = blockIdx.x; w < W; w += G) {
       const Item it = item_at(w, R, C, KS, KB, BM);
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
 #pragma unroll
@@ -321,8 +332,12 @@ __global__ __launch_bounds__(kTileWaves * 64) void gemm_tiled_kernel(
           wait_lds();
         bar();  // ... and every wave's; and the stage of the previous group is read by no one
         if (kCopy) issue_next(&stg[cur == 0 ? S - 1 : cur - 1]);  // into the stage freed by the previous group
-        compute(&stg[cur]);
+        if (!kDed || !kCopy) compute(&stg[cur]);
         cur = cur + 1 == S ? 0 : cur + 1;
+      }
+      if (kDed && kCopy) {
+        if (kGateUp) bar();  // the epilogue's
+        continue;
       }
 
       if (col_s != nullptr) {
@@ -334,7 +349,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void gemm_tiled_kernel(
                                     : static_cast<int64_t>(it.col) * BNR + WC * wn + 16 * j + 4 * q;
           const float4 cs = (kGateUp || n < N) ? *reinterpret_cast<const float4*>(col_s + n) : make_float4(0, 0, 0, 0);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
+          for (int i = 0; i < MT; ++i) {
             acc[i][j][0] *= cs.x;
             acc[i][j][1] *= cs.y;
             acc[i][j][2] *= cs.z;
@@ -345,9 +360,9 @@ __global__ __launch_bounds__(kTileWaves * 64) void gemm_tiled_kernel(
       if (kGateUp) {
         // ---- SwiGLU: h = SiLU(g) * u; lanes hold matching gate (j) and up
         // (j + NJ/2) values; h replaces g in acc
-        float am[4];
+        float am[MT];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < MT; ++i) {
           float a = 0.0f;
 #pragma unroll
           for (int j = 0; j < NJ / 2; ++j)
@@ -364,15 +379,15 @@ __global__ __launch_bounds__(kTileWaves * 64) void gemm_tiled_kernel(
         }
         if (q == 0) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) sRed[wn][64 * wm + 16 * i + lr] = am[i];
+          for (int i = 0; i < MT; ++i) sRed[wn][WR * wm + 16 * i + lr] = am[i];
         }
         wait_lds();
         bar();  // the row amax of every wavefront of the band is in LDS
         // ---- 1x128 quantization of each row's h-group (without hq: h only)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < MT; ++i) {
           if (hq == nullptr) {
-            const int64_t grow = static_cast<int64_t>(it.m0) + 64 * wm + 16 * i + lr;
+            const int64_t grow = static_cast<int64_t>(it.m0) + WR * wm + 16 * i + lr;
             if (grow < M) {
 #pragma unroll
               for (int j = 0; j < NJ / 2; ++j)
@@ -382,7 +397,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void gemm_tiled_kernel(
             }
             continue;
           }
-          const int row = 64 * wm + 16 * i + lr;
+          const int row = WR * wm + 16 * i + lr;
           const int64_t grow = static_cast<int64_t>(it.m0) + row;
           float amax = sRed[0][row];
 #pragma unroll
@@ -416,8 +431,8 @@ __global__ __launch_bounds__(kTileWaves * 64) void gemm_tiled_kernel(
         // partial sum of this K split
         const int64_t n0 = static_cast<int64_t>(it.col) * BNR;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int64_t row = static_cast<int64_t>(it.m0) + 64 * wm + 16 * i + lr;
+        for (int i = 0; i < MT; ++i) {
+          const int64_t row = static_cast<int64_t>(it.m0) + WR * wm + 16 * i + lr;
           if (row >= M) continue;
 #pragma unroll
           for (int j = 0; j < NJ; ++j) {
@@ -439,7 +454,7 @@ __global__ __launch_bounds__(kTileWaves * 64) void gemm_tiled_kernel(
     }
     if (kCopy) wait_vm<0>();  // the trailing repeat copies
   };
-  if (wave < kCopyWaves)
+  if (kDed ? wave >= kTileWaves : wave < kCopyWaves)
     run(std::true_type{});
   else
     run(std::false_type{});
@@ -459,19 +474,6 @@ int device_cu_count() {
   return n;
 }
 
-template __global__ void gemm_tiled_kernel<true, 256>(const uint8_t*, const float*, const uint8_t*, const float*,
-                                                     uint8_t*, float*, float*, uint16_t*, float*, float*, const float*, int64_t,
-                                                     int64_t, int64_t, int64_t, int, int);
-template __global__ void gemm_tiled_kernel<true, 128>(const uint8_t*, const float*, const uint8_t*, const float*,
-                                                     uint8_t*, float*, float*, uint16_t*, float*, float*, const float*, int64_t,
-                                                     int64_t, int64_t, int64_t, int, int);
-template __global__ void gemm_tiled_kernel<false, 256>(const uint8_t*, const float*, const uint8_t*, const float*,
-                                                      uint8_t*, float*, float*, uint16_t*, float*, float*, const float*, int64_t,
-                                                      int64_t, int64_t, int64_t, int, int);
-template __global__ void gemm_tiled_kernel<false, 128>(const uint8_t*, const float*, const uint8_t*, const float*,
-                                                      uint8_t*, float*, float*, uint16_t*, float*, float*, const float*, int64_t,
-                                                      int64_t, int64_t, int64_t, int, int);
-
 namespace {
 
 // out = RNE_bf16(sum of the KS partials, in split order); 4 columns per thread.
@@ -488,7 +490,7 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(const float* __restri
   if (out_tap != nullptr) *reinterpret_cast<float4*>(out_tap + e) = acc;
 }
 
-template <bool kGateUp, int BM>
+template <bool kGateUp, int BM, int BNR>
 hipError_t launch_tiled(hipStream_t st, const uint8_t* aq, const float* as, const uint8_t* bq, const float* bs,
                         uint8_t* hq, float* hs, float* h_tap, uint16_t* out, float* out_tap, float* part, int64_t M,
                         int64_t K, int64_t N, int64_t I, int KS, const float* col_s) {
@@ -496,35 +498,31 @@ hipError_t launch_tiled(hipStream_t st, const uint8_t* aq, const float* as, cons
   const int W = static_cast<int>(((M + BM - 1) / BM) * ny * KS);  // work items (< 2^31 by the size limits)
   // one workgroup per CU (the LDS ring allows no more)
   const int G = W < device_cu_count() ? W : device_cu_count();
-  hipLaunchKernelGGL((gemm_tiled_kernel<kGateUp, BM>), dim3(static_cast<unsigned>(G)), dim3(kTileWaves * 64), 0, st,
-                     aq, as, bq, bs, hq, hs, h_tap, out, out_tap, part, col_s, M, K, N, I, KS, W);
+  hipLaunchKernelGGL((gemm_tiled_kernel<kGateUp, BM, BNR>), dim3(static_cast<unsigned>(G)), dim3(tile_threads(BM)), 0,
+                     st, aq, as, bq, bs, hq, hs, h_tap, out, out_tap, part, col_s, M, K, N, I, KS, W);
   return hipGetLastError();
 }
 
-// Row-tile height, by rounds of one workgroup per CU: 256-row tiles unless
-// 128-row tiles fill no more rounds. A round of 256-row tiles (twice the
-// work) takes about 1.4-1.6 times a round of 128-row tiles over the same K,
-// so fewer rounds of the larger tile win whenever the smaller one needs more;
-// with equal rounds the smaller tile leaves fewer CUs idle (and the down GEMM
-// then splits K when it has fewer tiles than CUs).
-bool use_bm256(int64_t M, int64_t col_tiles) {
-  const int64_t cus = device_cu_count();
-  const int64_t r256 = (((M + 255) / 256) * col_tiles + cus - 1) / cus;
-  const int64_t r128 = (((M + 127) / 128) * col_tiles + cus - 1) / cus;
-  return r128 > r256;
-}
-
-// K splits of the down GEMM: as many as fit in one round of one workgroup
-// per CU, each split at least 16 K-groups long. Rounding up instead spills a
-// few items into a second round: at H = 4096, I = 12288, M = 700 (96 tiles)
-// 3 splits took 75.5 us against 56.8 us for 2.
+// The split-K partials the workspace has room for: at 128 x 256 tiles as many
+// splits as fit in one round of one workgroup per CU, each at least 16
+// K-groups long (1 where 256-row tiles need fewer rounds).
 int down_splits(int64_t M, int64_t H, int64_t I) {
-  const int64_t tiles = ((M + 127) / 128) * ((H + BNR - 1) / BNR), cus = device_cu_count();
-  if (use_bm256(M, (H + BNR - 1) / BNR) || tiles >= cus) return 1;
+  const int64_t ct = (H + 255) / 256, cus = device_cu_count(), tiles = ((M + 127) / 128) * ct;
+  const int64_t r256 = (((M + 255) / 256) * ct + cus - 1) / cus, r128 = (tiles + cus - 1) / cus;
+  if (r128 > r256 || tiles >= cus) return 1;
   int64_t ks = cus / tiles;
   const int64_t max_ks = (I / 128) / 16;
   if (ks > max_ks) ks = max_ks;
   return ks < 1 ? 1 : static_cast<int>(ks);
+}
+
+// Time of the K loops of a launch of `items` work items of n K-groups each, in
+// us: rounds of one workgroup per CU, and a K-group's time c0 + c1 f on a
+// device with a fraction f of its workgroup slots in use (the clock falls and
+// the memory fills as more CUs work).
+double loops_us(int64_t items, int64_t n, double c0, double c1) {
+  const int64_t cus = device_cu_count(), rounds = (items + cus - 1) / cus;
+  return static_cast<double>(rounds * n) * (c0 + c1 * static_cast<double>(items) / static_cast<double>(rounds * cus));
 }
 
 }  // namespace
@@ -537,23 +535,73 @@ size_t tiled_down_ws_bytes(int64_t M, int64_t H, int64_t I) {
 hipError_t launch_gateup_tiled(hipStream_t st, const uint8_t* xq, const float* xs, const uint8_t* wq,
                                const float* ws, uint8_t* hq, float* hs, float* h_tap, int64_t M, int64_t H,
                                int64_t I, const float* col_s) {
-  if (use_bm256(M, I / 128))
-    return launch_tiled<true, 256>(st, xq, xs, wq, ws, hq, hs, h_tap, nullptr, nullptr, nullptr, M, H, 2 * I, I, 1,
-                                   col_s);
-  return launch_tiled<true, 128>(st, xq, xs, wq, ws, hq, hs, h_tap, nullptr, nullptr, nullptr, M, H, 2 * I, I, 1,
-                                 col_s);
+  // Row-tile height: the least loop time. Every height gives the same bytes (an
+  // element's K-groups are added in the same order). K-group times fitted to
+  // sweeps at H = 512..8192, I = 6144..24576 and M = 65..2048; at H = 4096, I =
+  // 12288 the kernel takes, at the height chosen and at the better of 128 and
+  // 256 rows: M = 128 29 and 35 us (64 rows), 192 32 and 36 (96), 333 46 and 52
+  // (192), 700 87 and 98 (192), 1536 138 and 160 (192).
+  constexpr int kHeights[5] = {256, 192, 128, 96, 64};
+  constexpr double kGroup[5][2] = {{1.1, 0.73}, {0.92, 0.55}, {0.72, 0.36}, {0.57, 0.33}, {0.45, 0.35}};
+  int pick = 0;
+  double best = 0.0;
+  for (int t = 0; t < 5; ++t) {
+    const double us = loops_us(((M + kHeights[t] - 1) / kHeights[t]) * (I / 128), H / 128, kGroup[t][0], kGroup[t][1]);
+    if (t == 0 || us < best) pick = t, best = us;
+  }
+#define GU(BM_)                                                                                                    \
+  return launch_tiled<true, BM_, 256>(st, xq, xs, wq, ws, hq, hs, h_tap, nullptr, nullptr, nullptr, M, H, 2 * I, I, 1, \
+                                      col_s)
+  switch (kHeights[pick]) {
+    case 64: GU(64);
+    case 96: GU(96);
+    case 128: GU(128);
+    case 192: GU(192);
+    default: GU(256);
+  }
+#undef GU
 }
 
 hipError_t launch_down_tiled(hipStream_t st, const uint8_t* hq, const float* hs, const uint8_t* wq, const float* ws,
                              uint16_t* out, float* out_tap, int64_t M, int64_t H, int64_t I, void* ws_buf,
                              const float* col_s) {
-  if (use_bm256(M, (H + BNR - 1) / BNR))
-    return launch_tiled<false, 256>(st, hq, hs, wq, ws, nullptr, nullptr, nullptr, out, out_tap, nullptr, M, I, H, I,
-                                    1, col_s);
-  const int ks = down_splits(M, H, I);
+  // Tile shape and K splits (up to the partials the workspace holds): the
+  // least of start-up + loops + the partials' reduction (a launch, and writing
+  // and reading them). Fitted to sweeps of all shapes and splits at H = 512..4096, I =
+  // 3072..12288, M = 65..4096; at H = 4096, I = 12288 the chosen one and 128 x
+  // 256 tiles alone take: M = 128 18.4 (64 x 128, 4 splits) and 25.2 us, M = 256
+  // 25.1 (128 x 128, 4) and 29.7, M = 512 37.3 (128 x 128, 2) and 39.6; at H =
+  // 1024, I = 3072, M = 512 12.5 (64 x 128, 1) and 24.1.
+  struct Shape {
+    int bm, bn;
+    double start, c0, c1;
+  };
+  constexpr Shape kShapes[4] = {
+      {256, 256, 9.0, 1.17, 0.53}, {128, 256, 6.3, 0.68, 0.37}, {128, 128, 5.7, 0.40, 0.15}, {64, 128, 5.8, 0.28, 0.06}};
+  const int ks_max = down_splits(M, H, I);
+  int pick = 0, ks = 1;
+  double best = 0.0;
+  for (int t = 0; t < 4; ++t) {
+    const Shape& s = kShapes[t];
+    const int64_t tiles = ((M + s.bm - 1) / s.bm) * ((H + s.bn - 1) / s.bn);
+    for (int k = 1; k <= (s.bm == 256 ? 1 : ks_max); ++k) {
+      const double us = s.start + loops_us(tiles * k, (I / 128 + k - 1) / k, s.c0, s.c1) +
+                        (k > 1 ? 2.5 + (4.0 * k + 2.0) * static_cast<double>(M * H) / 7e6 : 0.0);
+      if ((t == 0 && k == 1) || us < best) pick = t, ks = k, best = us;
+    }
+  }
   float* part = static_cast<float*>(ws_buf);
-  hipError_t e = launch_tiled<false, 128>(st, hq, hs, wq, ws, nullptr, nullptr, nullptr, out, out_tap, part, M, I, H,
-                                          I, ks, col_s);
+  hipError_t e = hipSuccess;
+#define DN(BM_, BN_)                                                                                              \
+  e = launch_tiled<false, BM_, BN_>(st, hq, hs, wq, ws, nullptr, nullptr, nullptr, out, out_tap, part, M, I, H, I, ks, \
+                                    col_s)
+  switch (pick) {
+    case 0: DN(256, 256); break;
+    case 1: DN(128, 256); break;
+    case 2: DN(128, 128); break;
+    default: DN(64, 128); break;
+  }
+#undef DN
   if (e != hipSuccess || ks == 1) return e;
   const int64_t mn = M * H;
   hipLaunchKernelGGL(split_reduce_kernel, dim3(static_cast<unsigned>((mn / 4 + 255) / 256)), dim3(256), 0, st, part,

@@ -508,6 +508,39 @@ def test_split_k_down_sampled(big_layer, M, ks):
     _say("split-K M=%d: gate/up %s; down error %.2e, %.3f of the model tolerance" % (M, g, e, d))
 
 
+@pytest.mark.parametrize("M", [100, 190, 333])
+def test_tile_heights_sampled(big_layer, M):
+    """The tiled GEMMs' other tile shapes, each with a ragged last row tile
+    (gate/up heights 64, 96 and 192; down 64 x 128 and 128 x 128 with K
+    splits), oracle-checked on sampled rows, the tile edges included."""
+    w = synth.Workload(98, "heights", M, 4096, 12288, act="outlier", outlier_ratio=0.01)
+    rows = lambda m: np.unique([r for r in (0, 63, 64, 95, 96, 191, 192, m - 1) if r < m])
+    g, e, d = _full_size_case(big_layer, w, 0, rows, 0)
+    _say("tile heights M=%d: gate/up %s; down error %.2e, %.3f of the model tolerance" % (M, g, e, d))
+
+
+def test_gateup_bytes_do_not_depend_on_the_tile_height(big_layer):
+    """An element's K-groups are added in the same order at every tile height,
+    so the codes and scales of a row are the same bytes in calls of 65, 190,
+    256, 333, 512 and 700 rows (heights 64, 96, 128, 192, 256 and 192)."""
+    w = synth.Workload(98, "heights", 700, 4096, 12288, act="outlier", outlier_ratio=0.01)
+    x = dev_bf16(synth.make_x(w, layer=1))
+    ref = None
+    for M in (700, 512, 333, 256, 190, 65):
+        xq = torch.empty((M, 4096), dtype=torch.uint8, device=DEV)
+        xs = torch.empty((32, M), dtype=torch.float32, device=DEV)
+        hq = torch.full((M, 12288), 0xFF, dtype=torch.uint8, device=DEV)
+        hs = torch.full((96, M), float("nan"), dtype=torch.float32, device=DEV)
+        _say("gate/up M=%d" % M)
+        lc.lacache_rmsnorm_quant(x[:M], big_layer.norm_w, xq, xs)
+        lc.lacache_gateup_swiglu_quant(xq, xs, big_layer.wgu_q, big_layer.wgu_s, hq, hs)
+        torch.cuda.synchronize()
+        if ref is None:
+            ref = (hq, hs)
+        assert torch.equal(hq, ref[0][:M]), M
+        assert torch.equal(hs.view(torch.int32), ref[1][:, :M].view(torch.int32)), M
+
+
 @pytest.mark.parametrize("M,H,I", [(5, 16384, 1024), (5, 256, 65536)])
 def test_maximum_h_and_i(M, H, I):
     """The largest H (16384) and the largest I (65536) the library takes, each
