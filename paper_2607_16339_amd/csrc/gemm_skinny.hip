@@ -6,18 +6,18 @@
 // an output tile is split over several wavefronts of a workgroup, whose fp32
 // partials are added in LDS in a fixed order.
 //
-// gate/up: a workgroup owns 3 (gate, up) slab pairs x 4 K parts (one
-//          wavefront each), or at 33..64 rows 6 pairs x 2 parts. The
-//          activation codes are copied into LDS once per workgroup (up to
-//          32 rows over all of K; 33..64 rows over one half of K, the halves
-//          in two workgroups); the weights go global -> VGPRs with non-temporal
+// gate/up: a workgroup owns P (gate, up) slab pairs x 12 / P K parts (one
+//          wavefront each), P = 1, 2 or 3 by I, or 6 x 2 where it takes one
+//          half of K. The activation codes are copied into LDS once per
+//          workgroup (over all of K where they fit, else, at 33..64 rows,
+//          over one half of K, the halves in two workgroups); the weights go global -> VGPRs with non-temporal
 //          16-byte loads straight into the MFMA operand layout, a ring of
 //          K-groups per wavefront in straight-line code (the compiler waits
 //          for one K-group's registers at a time). The weight tile layout
 //          (wtile_off) makes each load read 1 KB contiguous; on a row-major
 //          matrix the same operand layout reads 16 rows x 64 bytes per load,
 //          which streams about 25 % slower on gfx950. SwiGLU after the
-//          partials are added; h stored as fp32 (33..64 rows: the gate and
+//          partials are added; h stored as fp32 (K halves: the gate and
 //          up sums of each K half, added by the second kernel before
 //          SwiGLU). A second kernel quantizes h per 1x128 group (a group's columns come from several workgroups,
 //          and stream order is the cheapest way to make all of them visible:
@@ -70,10 +70,7 @@ __device__ __forceinline__ v8i cat_frag(u4v lo, u4v hi) {
 // gate and up sums to part[y] [M][2I]; the h-quantization kernel adds the two
 // halves in that order and applies SwiGLU.
 constexpr int kVuWaves = 12;
-#ifndef LACACHE_NH2_PAIRS
-#define LACACHE_NH2_PAIRS 6
-#endif
-constexpr int kNh2Pairs = LACACHE_NH2_PAIRS;  // slab pairs per workgroup at 33..64 rows
+constexpr int kNh2Pairs = 6;  // slab pairs per workgroup on K halves
 constexpr int kVuXBytes = 64 * (2048 + 16);  // activation rows x (K range + 16) bytes, at most
 constexpr int kVuMaxNkb = 64;                 // K-groups of the whole K
 constexpr int kVuScales = 2048;               // activation scales of a workgroup's K range, at most
@@ -86,7 +83,7 @@ __global__ __launch_bounds__(kVuWaves * 64) void skinny_gateup_kernel(
   constexpr int R = MT * 16;  // activation rows (padded)
   static_assert(NH == 1 || NH == 2, "K pieces");
   static_assert(PAIRS * KQ == kVuWaves, "one wavefront per (pair, part)");
-  constexpr int kMaxNkw = kVuMaxNkb / KQ;  // K-groups of one part
+  constexpr int kMaxNkw = (kVuMaxNkb + KQ - 1) / KQ;  // K-groups of one part
   __shared__ __align__(16) uint8_t sX[kVuXBytes];  // codes [R][Kw + 16]; later the partials
   __shared__ __align__(16) float sXs[kVuScales];   // activation scales [Kw/128][R]
   __shared__ float sWs[kVuWaves][2][kMaxNkw];    // each wavefront's (gate, up) block scales
@@ -117,25 +114,31 @@ __global__ __launch_bounds__(kVuWaves * 64) void skinny_gateup_kernel(
   constexpr int XCH = (kVuXBytes / 16 + kVuWaves * 64 - 1) / (kVuWaves * 64);  // chunks per thread, at most
   const int cpr = KBW * 8;  // chunks per row
   const int nch = static_cast<int>(M) * cpr;
-  // c / cpr for c < 2^14: the float estimate is off by at most one
-  const float rcpr = 1.0f / static_cast<float>(cpr > 0 ? cpr : 1);
-  auto row_of = [&](int c) {
-    int r = static_cast<int>(static_cast<float>(c) * rcpr);
-    r -= r * cpr > c ? 1 : 0;
-    r += (r + 1) * cpr <= c ? 1 : 0;
-    return r;
-  };
+  // chunk t's row and column by a division (the float estimate of t / cpr is
+  // off by at most one), the next ones (768 chunks on) by steps of it. Passes
+  // that no lane of the wavefront needs are skipped: at K = 256 only the first
+  // of the 11 has anything to do, and the address arithmetic of the others took
+  // longer than the whole of the kernel's other work.
+  const int dr = kVuWaves * 64 / (cpr > 0 ? cpr : 1), dc = kVuWaves * 64 - dr * cpr;
+  int row0 = static_cast<int>(static_cast<float>(t) * (1.0f / static_cast<float>(cpr > 0 ? cpr : 1)));
+  row0 -= row0 * cpr > t ? 1 : 0;
+  row0 += (row0 + 1) * cpr <= t ? 1 : 0;
   u4v xc[XCH];
+  {
+    int row = row0, col = t - row0 * cpr;
 #pragma unroll
-  for (int j = 0; j < XCH; ++j) {
-    const int c = t + j * kVuWaves * 64;
-    if (c < nch) {
-      // NH = 1: the rows are contiguous; NH = 2: row r's range starts at r K + kbw 128
-      const uint32_t off = NH == 1 ? 16u * static_cast<uint32_t>(c)
-                                   : static_cast<uint32_t>(row_of(c)) * static_cast<uint32_t>(K) +
-                                         static_cast<uint32_t>(kbw) * 128u +
-                                         16u * static_cast<uint32_t>(c - row_of(c) * cpr);
-      xc[j] = *reinterpret_cast<const u4v*>(aq + off);
+    for (int j = 0; j < XCH; ++j) {
+      if (wave * 64 + j * kVuWaves * 64 < nch) {  // uniform
+        // NH = 1: the rows are contiguous; NH = 2: row r's range starts at r K + kbw 128
+        const uint32_t off = NH == 1 ? 16u * static_cast<uint32_t>(t + j * kVuWaves * 64)
+                                     : static_cast<uint32_t>(row) * static_cast<uint32_t>(K) +
+                                           static_cast<uint32_t>(kbw) * 128u + 16u * static_cast<uint32_t>(col);
+        if (t + j * kVuWaves * 64 < nch) xc[j] = *reinterpret_cast<const u4v*>(aq + off);
+        if (NH != 1) {
+          row += dr, col += dc;
+          if (col >= cpr) col -= cpr, ++row;
+        }
+      }
     }
   }
   // ---- 2. scales into registers
@@ -145,7 +148,9 @@ __global__ __launch_bounds__(kVuWaves * 64) void skinny_gateup_kernel(
   for (int j = 0; j < XPT; ++j) {
     const int i = t + j * kVuWaves * 64;
     const int kb = i / R, m = i % R;
-    xv[j] = (kb < KBW && m < M) ? as[static_cast<int64_t>(kbw + kb) * M + m] : 0.0f;
+    xv[j] = 0.0f;
+    if (wave * 64 + j * kVuWaves * 64 < KBW * R)  // uniform
+      xv[j] = (kb < KBW && m < M) ? as[static_cast<int64_t>(kbw + kb) * M + m] : 0.0f;
   }
   const int64_t wrow[2] = {16 * p0, I + 16 * p0};
   const int sn = lane >> 5, sj = lane & 31;
@@ -177,10 +182,17 @@ __global__ __launch_bounds__(kVuWaves * 64) void skinny_gateup_kernel(
   for (int u = 0; u < DR; ++u) issue(u, u);
   __builtin_amdgcn_sched_barrier(0);
 
+  {
+    int row = row0, col = t - row0 * cpr;
 #pragma unroll
-  for (int j = 0; j < XCH; ++j) {
-    const int c = t + j * kVuWaves * 64;
-    if (c < nch) *reinterpret_cast<u4v*>(sX + 16 * (c + row_of(c))) = xc[j];
+    for (int j = 0; j < XCH; ++j) {
+      const int c = t + j * kVuWaves * 64;
+      if (wave * 64 + j * kVuWaves * 64 < nch) {  // uniform
+        if (c < nch) *reinterpret_cast<u4v*>(sX + 16 * (c + row)) = xc[j];
+        row += dr, col += dc;
+        if (col >= cpr) col -= cpr, ++row;
+      }
+    }
   }
 #pragma unroll
   for (int j = 0; j < XPT; ++j) {
@@ -366,13 +378,15 @@ __global__ __launch_bounds__(SPLIT * 64) void skinny_down_kernel(
 #pragma unroll
     for (int j = 0; j < XPT; ++j) {
       const int i = lane + 64 * j, kb = i / RA, m = i % RA;
-      xv[j] = (i < nkb * RA && m < M) ? as[(kb0 + kb) * M + m] : 0.0f;
+      xv[j] = 0.0f;
+      if (64 * j < nkb * RA)  // uniform: passes past the part's K-groups are skipped
+        xv[j] = (i < nkb * RA && m < M) ? as[(kb0 + kb) * M + m] : 0.0f;
     }
     const float wv = lane < nkb ? ws[(n0 / 128) * KB + kb0 + lane] : 0.0f;
 #pragma unroll
     for (int j = 0; j < XPT; ++j) {
       const int i = lane + 64 * j;
-      if (i < nkb * RA) sXs[wave][i] = xv[j];
+      if (64 * j < nkb * RA && i < nkb * RA) sXs[wave][i] = xv[j];
     }
     if (lane < nkb) sWs[wave][lane] = wv;
   }
@@ -502,11 +516,14 @@ __global__ __launch_bounds__(256) void skinny_hquant2_kernel(const float* __rest
 // Shapes the kernels cover: M <= 32 activation rows over all of K (NH = 1),
 // or 33..64 rows over half of K (NH = 2), that fit the gate/up kernel's LDS
 // and scale tables; down: K parts that fit its scale tables.
-int gateup_halves(int64_t M) { return M <= 32 ? 1 : 2; }
+bool gateup_fits(int64_t R, int64_t kbw) { return R * (kbw * 128 + 16) <= kVuXBytes && kbw * R <= kVuScales; }
+// K pieces: 1, or 2 where 33..64 rows over all of K do not fit (one piece needs
+// no partial sums in memory: 64 rows at H = 2048, I = 6144 31.9 -> 27.8 us)
+int gateup_halves(int64_t M, int64_t K) { return M <= 32 || gateup_fits((M + 15) / 16 * 16, K / 128) ? 1 : 2; }
 bool gateup_v_ok(int64_t M, int64_t K) {
-  const int64_t R = ((M + 15) / 16) * 16, KB = K / 128, nh = gateup_halves(M);
+  const int64_t R = ((M + 15) / 16) * 16, KB = K / 128, nh = gateup_halves(M, K);
   const int64_t kbw = (KB + nh - 1) / nh;  // K-groups of the larger piece
-  return M <= 64 && KB <= kVuMaxNkb && R * (kbw * 128 + 16) <= kVuXBytes && kbw * R <= kVuScales;
+  return M <= 64 && KB <= kVuMaxNkb && gateup_fits(R, kbw);
 }
 bool down_ok(int64_t M, int64_t K) { return M <= 64 && K / 128 <= kDnSplit * kDnMaxNkbW; }
 
@@ -518,7 +535,8 @@ bool skinny_supported(int64_t M, int64_t H, int64_t I) {
 
 size_t skinny_gateup_ws_bytes(int64_t M, int64_t I) {
   // h [M x I] fp32, or for 33..64 rows the two K halves' gate and up sums [2][M][2I]
-  const size_t n = static_cast<size_t>(M) * static_cast<size_t>(I) * (gateup_halves(M) == 1 ? 1 : 4);
+  // (not needed where all of K fits)
+  const size_t n = static_cast<size_t>(M) * static_cast<size_t>(I) * (M <= 32 ? 1 : 4);
   return ((n * sizeof(float) + 255) / 256) * 256;
 }
 
@@ -531,25 +549,44 @@ hipError_t launch_gateup_skinny(hipStream_t st, const uint8_t* xq, const float* 
   const dim3 block(kVuWaves * 64);
   const int64_t groups = M * (I / 128);
   const dim3 qgrid(static_cast<unsigned>((groups + 15) / 16)), qblock(256);
-  // up to 32 rows: 3 slab pairs x 4 K parts per workgroup (256 workgroups at
-  // I = 12288); 33..64 rows, each workgroup on one K half: 6 pairs x 2 parts,
-  // so the two halves still make one round of one workgroup per CU
-  const unsigned gx1 = static_cast<unsigned>((I / 16 + 2) / 3), gx2 = static_cast<unsigned>((I / 16 + kNh2Pairs - 1) / kNh2Pairs);
-  if (M <= 16)
-    hipLaunchKernelGGL((skinny_gateup_kernel<1, kVuDR, 1, 3, 4>), dim3(gx1), block, 0, st, xq, xs, wq, ws, h_tap, hbuf, M, H,
-                       I);
-  else if (M <= 32)
-    hipLaunchKernelGGL((skinny_gateup_kernel<2, kVuDR, 1, 3, 4>), dim3(gx1), block, 0, st, xq, xs, wq, ws, h_tap, hbuf, M, H,
-                       I);
-  else if (M <= 48)
-    hipLaunchKernelGGL((skinny_gateup_kernel<3, kVuDR, 2, kNh2Pairs, kVuWaves / kNh2Pairs>), dim3(gx2, 2), block, 0, st, xq,
-                       xs, wq, ws, h_tap, hbuf, M, H, I);
-  else
-    hipLaunchKernelGGL((skinny_gateup_kernel<4, kVuDR, 2, kNh2Pairs, kVuWaves / kNh2Pairs>), dim3(gx2, 2), block, 0, st, xq,
-                       xs, wq, ws, h_tap, hbuf, M, H, I);
+  const bool one = gateup_halves(M, H) == 1;
+  const int mt = static_cast<int>((M + 15) / 16);
+  // all of K per workgroup: the fewest slab pairs per workgroup (3, 2 or 1, the
+  // 12 wavefronts then splitting K into 4, 6 or 12 parts) whose workgroups
+  // still start in one round, so that a narrow layer streams through more
+  // CUs (whole FFN at one row, 3 pairs -> this rule: H = 4096, I = 3968 23.6 ->
+  // 20.4 us, H = 8192, I = 512 29.6 -> 21.1); two K halves: 6 pairs x 2 parts,
+  // one round at I = 12288
+  const int64_t cus = device_cu_count();
+  const int pairs = I / 16 <= cus ? 1 : (I / 32 <= cus ? 2 : 3);
+  const unsigned gx = static_cast<unsigned>((I / 16 + (one ? pairs : kNh2Pairs) - 1) / (one ? pairs : kNh2Pairs));
+#define SG(MT_, NH_, P_)                                                                                          \
+  hipLaunchKernelGGL((skinny_gateup_kernel<MT_, kVuDR, NH_, P_, kVuWaves / P_>), dim3(gx, NH_), block, 0, st, xq, xs, \
+                     wq, ws, h_tap, hbuf, M, H, I)
+#define SG1(P_)          \
+  switch (mt) {          \
+    case 1: SG(1, 1, P_); break; \
+    case 2: SG(2, 1, P_); break; \
+    case 3: SG(3, 1, P_); break; \
+    default: SG(4, 1, P_); break; \
+  }
+  if (!one) {
+    if (mt == 3)
+      SG(3, 2, kNh2Pairs);
+    else
+      SG(4, 2, kNh2Pairs);
+  } else if (pairs == 1) {
+    SG1(1)
+  } else if (pairs == 2) {
+    SG1(2)
+  } else {
+    SG1(3)
+  }
+#undef SG1
+#undef SG
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (M <= 32)
+  if (one)
     hipLaunchKernelGGL(skinny_hquant_kernel, qgrid, qblock, 0, st, hbuf, hq, hs, M, I);
   else
     hipLaunchKernelGGL(skinny_hquant2_kernel, qgrid, qblock, 0, st, hbuf, hq, hs, h_tap, M, I);

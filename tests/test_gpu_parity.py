@@ -430,6 +430,26 @@ def test_skinny_k_parts(M, H, I):
     check_down_model(host(t["hq"]), host(t["hs"]), wd_q, wd_s, host(t["out_tap"]))
 
 
+@pytest.mark.parametrize("M,H,I", [(5, 384, 4224), (48, 2560, 4224), (20, 256, 8320), (33, 128, 8192),
+                                   (64, 2048, 128), (64, 2176, 256)])
+def test_skinny_slab_pairs_per_workgroup(M, H, I):
+    """The gate/up kernel's other workgroup shapes: 2 slab pairs x 6 K parts
+    (I = 4224, 8192), 3 x 4 with a partial last workgroup (I = 8320) and 1 x
+    12 (I = 128, 256), at 33..64 rows with all of K in the LDS up to its
+    largest (H = 2560 at 48 rows, 2048 at 64) and with two K halves just above
+    (2176 at 64)."""
+    _say("skinny pairs M=%d H=%d I=%d" % (M, H, I))
+    lc.lacache_set_path_policy(1)
+    w = synth.Workload(91, "pairs", M, H, I, act="outlier", outlier_ratio=0.02)
+    lay = Layer(w, layer=1)
+    xb = synth.make_x(w, layer=1)
+    t = run_stages(dev_bf16(xb), lay, M, H, I)
+    wgu_q, wgu_s, _, _ = lay.host_weights()
+    check_norm_exact(xb, lay.bits["norm_w"], host(t["xq"]), host(t["xs"]))
+    check_requant_exact(host(t["h_tap"]), host(t["hq"]), host(t["hs"]))
+    check_gateup_model(host(t["xq"]), host(t["xs"]), wgu_q, wgu_s, I, host(t["h_tap"]), host(t["hq"]), host(t["hs"]))
+
+
 def _full_size_case(big_layer, w, step, rows_pick, policy):
     lc.lacache_set_path_policy(policy)
     xb = synth.make_x(w, layer=1, step=step)
