@@ -543,8 +543,12 @@ int lacache_ffn_fp8_g(void* stream, const uint16_t* x, const uint16_t* norm_w, c
   void* part = b;
   hipStream_t st = static_cast<hipStream_t>(stream);
   const bool tensor = granularity == LACACHE_GRAN_TENSOR;
-  RETURN_IF(hip_status(launch_rmsnorm_f32(st, x, norm_w, f, M, H)));
-  RETURN_IF(hip_status(launch_quant_rows_f32(st, f, xq, xs, rows, M, H, tensor)));
+  if (tensor) {
+    RETURN_IF(hip_status(launch_rmsnorm_f32(st, x, norm_w, f, M, H)));
+    RETURN_IF(hip_status(launch_quant_rows_f32(st, f, xq, xs, rows, M, H, tensor)));
+  } else {
+    RETURN_IF(hip_status(launch_rmsnorm_quant_token(st, x, norm_w, xq, xs, rows, M, H)));
+  }
   RETURN_IF(hip_status(launch_gateup_tiled(st, xq, xs, wgu_q, wgu_s, nullptr, nullptr, f, M, H, I, wgu_row_s)));
   RETURN_IF(hip_status(launch_quant_rows_f32(st, f, hq, hs, rows, M, I, tensor)));
   return hip_status(launch_down_tiled(st, hq, hs, wd_q, wd_s, out, nullptr, M, H, I, part, wd_row_s));

@@ -140,6 +140,8 @@ __device__ __forceinline__ float rms_inv(double ss, int H) {
 }
 // y = RN32(RN32(x w) r) of a chunk's 8 values (x w is exact in fp32).
 __device__ __forceinline__ void norm8(uint4 xv, uint4 wv, float r, float (&y)[8]);
+// Codes E(RN32(y / s)) of a chunk's 8 values at scale s (all 0x00 when s == 0).
+__device__ __forceinline__ void quant8(const float (&y)[8], float s, uint32_t& lo, uint32_t& hi);
 // The 1x128 group quantizer of a chunk's 8 values y within its 16-lane group:
 // returns the group scale s = RN32(max|y| / 448) and the codes E(RN32(y / s))
 // (all 0x00 when s == 0). Every lane of the 16 must call it.
@@ -265,18 +267,22 @@ __device__ __forceinline__ void norm8(uint4 xv, uint4 wv, float r, float (&y)[8]
   }
 }
 
-__device__ __forceinline__ float quant8_group(const float (&y)[8], uint32_t& lo, uint32_t& hi) {
-  float amax = 0.0f;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) amax = __builtin_fmaxf(amax, __builtin_fabsf(y[e]));
-  amax = max_xor<16>(amax);
-  const float s = amax / kE4M3Max;
+__device__ __forceinline__ void quant8(const float (&y)[8], float s, uint32_t& lo, uint32_t& hi) {
   lo = 0u;
   hi = 0u;
   if (s != 0.0f && !(scale_is_fast(s) && enc8_div_fast(y, fast_rcp(s), lo, hi))) {
     lo = enc4_e4m3(qdiv(y[0], s), qdiv(y[1], s), qdiv(y[2], s), qdiv(y[3], s));
     hi = enc4_e4m3(qdiv(y[4], s), qdiv(y[5], s), qdiv(y[6], s), qdiv(y[7], s));
   }
+}
+
+__device__ __forceinline__ float quant8_group(const float (&y)[8], uint32_t& lo, uint32_t& hi) {
+  float amax = 0.0f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) amax = __builtin_fmaxf(amax, __builtin_fabsf(y[e]));
+  amax = max_xor<16>(amax);
+  const float s = amax / kE4M3Max;
+  quant8(y, s, lo, hi);
   return s;
 }
 

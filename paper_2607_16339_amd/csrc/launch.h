@@ -17,6 +17,11 @@ hipError_t launch_rmsnorm_quant(hipStream_t st, uint16_t* x, const uint16_t* nw,
 // The RMSNorm alone, y = RN32(RN32(x * w) * r) in fp32 [M x H] (same
 // arithmetic as the fused quantizer).
 hipError_t launch_rmsnorm_f32(hipStream_t st, const uint16_t* x, const uint16_t* nw, float* y, int64_t M, int64_t H);
+// The RMSNorm and its per-token quantization: codes, the row's scale in every
+// group's place [H/128 x M] and in s_rows [M]; the bytes of launch_rmsnorm_f32
+// followed by launch_quant_rows_f32, in one kernel.
+hipError_t launch_rmsnorm_quant_token(hipStream_t st, const uint16_t* x, const uint16_t* nw, uint8_t* xq, float* xs,
+                                      float* s_rows, int64_t M, int64_t H);
 hipError_t launch_add_bf16(hipStream_t st, uint16_t* x, const uint16_t* y, int64_t n);
 
 // Coarse granularities: per-row (or, with per_tensor, one) scales of fp32

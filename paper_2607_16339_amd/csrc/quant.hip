@@ -97,9 +97,12 @@ hipError_t launch_pack_weights(hipStream_t st, const uint8_t* w, uint8_t* wt, in
 // float(y)), written back in place: each wavefront of the row writes its own
 // passes, after a workgroup barrier that follows every wavefront's reads of
 // the old row. With kF32Out the normalized row goes to
-// yf (fp32) instead of being quantized (the coarse-granularity paths).
+// yf (fp32) instead of being quantized (the per-tensor path). With kRowScale
+// the row has one scale (the per-token path): every wavefront of the row
+// normalizes all of it for its maximum, and the scale goes to yf[row] beside
+// its place in every group.
 // ---------------------------------------------------------------------------
-template <int T, bool kF32Out = false, bool kAdd = false>
+template <int T, bool kF32Out = false, bool kAdd = false, bool kRowScale = false>
 __global__ __launch_bounds__(256, T <= 8 && !kAdd ? 4 : 1) void rmsnorm_quant_kernel(uint16_t* x, const uint16_t* __restrict__ y,
                                                             const uint16_t* __restrict__ nw,
                                                             uint8_t* __restrict__ xq, float* __restrict__ xs,
@@ -155,6 +158,20 @@ __global__ __launch_bounds__(256, T <= 8 && !kAdd ? 4 : 1) void rmsnorm_quant_ke
     for (int t = 0; t < T; ++t)
       if ((t & ((1 << wpr_log2) - 1)) == part && t * 64 + lane < nchunk) xw[t * 64 + lane] = xv[t];
   }
+  float rsc = 0.0f;  // the row's scale
+  if constexpr (kRowScale) {
+    float amax = 0.0f;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      float v[8];
+      norm8(xv[t], wv[t], r, v);
+      if (t * 64 + lane < nchunk)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) amax = __builtin_fmaxf(amax, __builtin_fabsf(v[e]));
+    }
+    rsc = max_xor<64>(amax) / kE4M3Max;
+    if (part == 0 && lane == 0) yf[row] = rsc;
+  }
 #pragma unroll
   for (int t = 0; t < T; ++t) {
     if ((t & ((1 << wpr_log2) - 1)) != part) continue;  // uniform
@@ -171,7 +188,13 @@ __global__ __launch_bounds__(256, T <= 8 && !kAdd ? 4 : 1) void rmsnorm_quant_ke
       continue;
     }
     uint32_t lo, hi;
-    const float s = quant8_group(y, lo, hi);
+    float s;
+    if constexpr (kRowScale) {
+      s = rsc;
+      quant8(y, s, lo, hi);
+    } else {
+      s = quant8_group(y, lo, hi);
+    }
     if (valid) {
       *reinterpret_cast<uint2*>(xq + row * H + 8 * c) = make_uint2(lo, hi);
       if ((lane & 15) == 0) xs[static_cast<int64_t>(c >> 4) * M + row] = s;
@@ -224,6 +247,27 @@ hipError_t launch_rmsnorm_f32(hipStream_t st, const uint16_t* x, const uint16_t*
   else if (T <= 16) NF(16);
   else NF(32);
 #undef NF
+  return hipGetLastError();
+}
+
+hipError_t launch_rmsnorm_quant_token(hipStream_t st, const uint16_t* x, const uint16_t* nw, uint8_t* xq, float* xs,
+                                      float* s_rows, int64_t M, int64_t H) {
+  const int T = static_cast<int>((H + 511) / 512);
+  const int wl = M > 1024 ? 0 : (T >= 4 ? 2 : (T >= 2 ? 1 : 0));  // as launch_rmsnorm_quant
+  const int per_block = wl > 0 ? (1 << wl) : 4;
+  const dim3 grid(static_cast<unsigned>(((M << wl) + per_block - 1) / per_block)), block(64 * per_block);
+  uint16_t* xr = const_cast<uint16_t*>(x);  // only read (no residual)
+  const int h = static_cast<int>(H);
+#define NT(T_)                                                                                                       \
+  hipLaunchKernelGGL((rmsnorm_quant_kernel<T_, false, false, true>), grid, block, 0, st, xr, nullptr, nw, xq, xs, M, h, \
+                     wl, s_rows)
+  if (T <= 1) NT(1);
+  else if (T <= 2) NT(2);
+  else if (T <= 4) NT(4);
+  else if (T <= 8) NT(8);
+  else if (T <= 16) NT(16);
+  else NT(32);
+#undef NT
   return hipGetLastError();
 }
 
