@@ -165,6 +165,28 @@ def test_single_block_and_extreme_scores():
         _check_close(r(c0, c1, mode), A.attention(q, k, v), v, "N=64 C=[%d,%d) mode %d" % (c0, c1, mode))
 
 
+@pytest.mark.parametrize("N,c0,c1", [(832, 100, 132), (768, 0, 64), (832, 700, 832), (832, 0, 832), (832, 64, 832),
+                                     (832, 0, 704), (768, 5, 5)])
+def test_key_blocks_shared_by_two_groups(N, c0, c1):
+    """Short calls of 12 and more key blocks (2 heads): the blocks inside U are
+    shared by two groups of wavefronts, odd and even counts, one block, none,
+    all of them; half a workgroup of rows past the end (N = 832). Every mode
+    against the oracle, and the three bit for bit."""
+    rng = np.random.default_rng(N + c0 + c1)
+    q, k, v = (synth.to_bf16_bits(rng.standard_normal((2, N, 128)).astype(np.float32) * s) for s in (1.5, 1.5, 1.0))
+    r = Run(q, k, v)
+    _say("two groups N=%d C=[%d,%d)" % (N, c0, c1))
+    plain = r(c0, c1, 2)
+    _check_close(plain, A.attention(q, k, v), v, "plain")
+    assert _bits_equal(r(c0, c1, 0), plain)
+    assert _bits_equal(r(c0, c1, 1), plain)
+    if c0 < c1:
+        for x in (q, k, v):
+            x[:, c0:c1] = synth.to_bf16_bits(rng.standard_normal((2, c1 - c0, 128)).astype(np.float32))
+        r.set_inputs(q, k, v)
+        assert _bits_equal(r(c0, c1, 1), r(c0, c1, 2))
+
+
 def test_batch8x1024_sampled_heads():
     """Full-size batched workload (256 heads x 1024 tokens), launched whole,
     checked on sampled heads against the oracle."""
