@@ -81,13 +81,6 @@ __device__ __forceinline__ bf8 read_tr2(const uint8_t* p0, const uint8_t* p1) {
   return __builtin_bit_cast(bf8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-// two fp32 -> bf16 (round to nearest even) in one v_cvt_pk_bf16_f32
-typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t pack_bf16_rne(float lo, float hi) {
-  const bf2 v = {static_cast<__bf16>(lo), static_cast<__bf16>(hi)};
-  return __builtin_bit_cast(uint32_t, v);
-}
-
 // Slot s of an XCD's chunk [lo, lo + n) of the head-major item list, with the
 // chunk's heavy items (query blocks j < nh of a head, which stream every key
 // block) first and its light ones after. Resume uses this order: a light item
@@ -279,10 +272,10 @@ __global__ __launch_bounds__(64 * W * NG, 2) void facache_attention_kernel(AttnA
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
       const int tt = ks >> 1, e0 = 8 * (ks & 1);
-      const uint4 w4 = make_uint4(pack_bf16_rne(sa[tt][e0 + 0], sa[tt][e0 + 1]),
-                                  pack_bf16_rne(sa[tt][e0 + 2], sa[tt][e0 + 3]),
-                                  pack_bf16_rne(sa[tt][e0 + 4], sa[tt][e0 + 5]),
-                                  pack_bf16_rne(sa[tt][e0 + 6], sa[tt][e0 + 7]));
+      const uint4 w4 = make_uint4(cvt_pk_bf16(sa[tt][e0 + 0], sa[tt][e0 + 1]),
+                                  cvt_pk_bf16(sa[tt][e0 + 2], sa[tt][e0 + 3]),
+                                  cvt_pk_bf16(sa[tt][e0 + 4], sa[tt][e0 + 5]),
+                                  cvt_pk_bf16(sa[tt][e0 + 6], sa[tt][e0 + 7]));
       pb[ks] = __builtin_bit_cast(bf8, w4);
     }
     // O~^T += V^T P^T (Eq. 6)
@@ -386,8 +379,8 @@ __global__ __launch_bounds__(64 * W * NG, 2) void facache_attention_kernel(AttnA
 #pragma unroll
     for (int b = 0; b < 4; ++b)
       *reinterpret_cast<uint2*>(a.o + sb * kD + 32 * dt + 8 * b + 4 * g) =
-          make_uint2(pack_bf16_rne(ot[dt][4 * b] * inv, ot[dt][4 * b + 1] * inv),
-                     pack_bf16_rne(ot[dt][4 * b + 2] * inv, ot[dt][4 * b + 3] * inv));
+          make_uint2(cvt_pk_bf16(ot[dt][4 * b] * inv, ot[dt][4 * b + 1] * inv),
+                     cvt_pk_bf16(ot[dt][4 * b + 2] * inv, ot[dt][4 * b + 3] * inv));
   if (a.lse != nullptr && g == 0) a.lse[sb] = (m + __log2f(lt)) * 0.69314718055994531f;
 }
 

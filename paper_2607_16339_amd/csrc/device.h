@@ -54,43 +54,12 @@ __device__ __forceinline__ uint32_t enc1_e4m3(float a) {
 // rounded fp32 division).
 __device__ __forceinline__ float qdiv(float y, float s) { return y / s; }
 
-// The same code, E(RN32(y / s)), from the hardware reciprocal rs = rcp(s)
-// (1 ulp): q0 = y * rs is within 2^-22 (relative) of y / s, so when the codes
-// of q0 * (1 - 2^-20) and q0 * (1 + 2^-20) agree, that is the code of every
-// value in between, RN32(y / s) included (the encoder is monotone). Otherwise
-// the value sits at an e4m3 rounding boundary and the correctly rounded
-// division decides. Requires s >= 2^-100 (see scale_is_fast).
-__device__ __forceinline__ uint32_t enc1_div_fast(float y, float s, float rs) {
-  const float q0 = y * rs;
-  const float d = __builtin_fabsf(q0) * 0x1p-20f;
-  const uint32_t w = static_cast<uint32_t>(__builtin_amdgcn_cvt_pk_fp8_f32(clip448(q0 - d), clip448(q0 + d), 0, false));
-  if ((w & 0xFFu) == ((w >> 8) & 0xFFu)) return w & 0xFFu;
-  return enc1_e4m3(y / s);
-}
 __device__ __forceinline__ bool scale_is_fast(float s) { return s >= 0x1p-100f; }
 
-// Eight values at once, branch-free: the codes of q0 * (1 -+ 2^-20) for
-// each value (q0 = y * rs), as in enc1_div_fast. Returns true when all eight
-// pairs agree; the codes in lo/hi are then E(RN32(y / s)). Otherwise the
-// caller redoes the eight with the correctly rounded division.
-__device__ __forceinline__ bool enc8_div_fast(const float (&y)[8], float rs, uint32_t& lo, uint32_t& hi) {
-  float m[8], p[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const float q0 = y[e] * rs;
-    const float d = __builtin_fabsf(q0) * 0x1p-20f;
-    m[e] = q0 - d;
-    p[e] = q0 + d;
-  }
-  lo = enc4_e4m3(m[0], m[1], m[2], m[3]);
-  hi = enc4_e4m3(m[4], m[5], m[6], m[7]);
-  const uint32_t lo2 = enc4_e4m3(p[0], p[1], p[2], p[3]);
-  const uint32_t hi2 = enc4_e4m3(p[4], p[5], p[6], p[7]);
-  return ((lo ^ lo2) | (hi ^ hi2)) == 0u;
-}
 __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 
-// The bracket of enc1_div_fast with the factors folded into the reciprocal:
+// The same code, E(RN32(y / s)), from the hardware reciprocal (1 ulp) where a
+// bracket around the quotient decides it:
 // rl = RN32(rcp(s) (1 - 2^-20)), rh = RN32(rcp(s) (1 + 2^-20)). For a group
 // with amax = max|y| and s = RN32(amax / 448) >= 2^-100, and rcp within 2^-22
 // of 1/s, every y of the group has
@@ -159,6 +128,15 @@ __device__ __forceinline__ uint32_t f32_to_bf16(float f) {
   if ((u & 0x7FFFFFFFu) > 0x7F800000u) return 0x7FC0u;
   u += 0x7FFFu + ((u >> 16) & 1u);
   return u >> 16;
+}
+
+// Two values -> bf16 in one v_cvt_pk_bf16_f32: the bits of f32_to_bf16 for
+// every fp32 value (checked over all of them); a NaN stays a NaN, with its own
+// sign and payload.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t cvt_pk_bf16(float lo, float hi) {
+  const bf16x2 v = {static_cast<__bf16>(lo), static_cast<__bf16>(hi)};
+  return __builtin_bit_cast(uint32_t, v);
 }
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
@@ -268,9 +246,14 @@ __device__ __forceinline__ void norm8(uint4 xv, uint4 wv, float r, float (&y)[8]
 }
 
 __device__ __forceinline__ void quant8(const float (&y)[8], float s, uint32_t& lo, uint32_t& hi) {
+  const FastQuant f = fast_quant(s);
+  const bool a = enc4_bracket(y[0], y[1], y[2], y[3], f, lo), b = enc4_bracket(y[4], y[5], y[6], y[7], f, hi);
+  // a NaN (of a NaN or infinite y) takes the slow path, where the clip decides it
+  const uint32_t nan = ((lo & 0x7F7F7F7Fu) + 0x01010101u) | ((hi & 0x7F7F7F7Fu) + 0x01010101u);
+  if (scale_is_fast(s) && a && b && (nan & 0x80808080u) == 0u) return;
   lo = 0u;
   hi = 0u;
-  if (s != 0.0f && !(scale_is_fast(s) && enc8_div_fast(y, fast_rcp(s), lo, hi))) {
+  if (s != 0.0f) {
     lo = enc4_e4m3(qdiv(y[0], s), qdiv(y[1], s), qdiv(y[2], s), qdiv(y[3], s));
     hi = enc4_e4m3(qdiv(y[4], s), qdiv(y[5], s), qdiv(y[6], s), qdiv(y[7], s));
   }

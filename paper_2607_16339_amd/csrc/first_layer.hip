@@ -31,12 +31,6 @@ namespace lacache {
 namespace {
 
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
-// two fp32 -> bf16, nearest-even, in one instruction
-__device__ __forceinline__ uint32_t cvt_pk_bf16(float lo, float hi) {
-  const bf2 v = {static_cast<__bf16>(lo), static_cast<__bf16>(hi)};
-  return __builtin_bit_cast(uint32_t, v);
-}
 
 // A row belongs to 1 << wpr_log2 wavefronts of a workgroup: each reads the row
 // and takes the whole sum (the fixed order is one chain of 8 T fp64 FMAs per

@@ -457,11 +457,8 @@ __global__ __launch_bounds__(256) void skinny_hquant_kernel(const float* __restr
   for (int e = 0; e < 8; ++e) m = __builtin_fmaxf(m, __builtin_fabsf(v[e]));
   m = max_xor<16>(m);
   const float s = m / kE4M3Max;
-  uint32_t lo = 0u, hi = 0u;
-  if (s != 0.0f && !(scale_is_fast(s) && enc8_div_fast(v, fast_rcp(s), lo, hi))) {
-    lo = enc4_e4m3(qdiv(v[0], s), qdiv(v[1], s), qdiv(v[2], s), qdiv(v[3], s));
-    hi = enc4_e4m3(qdiv(v[4], s), qdiv(v[5], s), qdiv(v[6], s), qdiv(v[7], s));
-  }
+  uint32_t lo, hi;
+  quant8(v, s, lo, hi);
   if (!ok) return;
   *reinterpret_cast<uint2*>(hq + row * I + g * 128 + part * 8) = make_uint2(lo, hi);
   if (part == 0) hs[g * M + row] = s;
@@ -499,11 +496,8 @@ __global__ __launch_bounds__(256) void skinny_hquant2_kernel(const float* __rest
   for (int e = 0; e < 8; ++e) m = __builtin_fmaxf(m, __builtin_fabsf(v[e]));
   m = max_xor<16>(m);
   const float s = m / kE4M3Max;
-  uint32_t lo = 0u, hi = 0u;
-  if (s != 0.0f && !(scale_is_fast(s) && enc8_div_fast(v, fast_rcp(s), lo, hi))) {
-    lo = enc4_e4m3(qdiv(v[0], s), qdiv(v[1], s), qdiv(v[2], s), qdiv(v[3], s));
-    hi = enc4_e4m3(qdiv(v[4], s), qdiv(v[5], s), qdiv(v[6], s), qdiv(v[7], s));
-  }
+  uint32_t lo, hi;
+  quant8(v, s, lo, hi);
   if (!ok) return;
   *reinterpret_cast<uint2*>(hq + row * I + c0) = make_uint2(lo, hi);
   if (sub == 0) hs[g * M + row] = s;

@@ -89,11 +89,8 @@ __global__ __launch_bounds__(256) void quant_rows_kernel(const T* __restrict__ v
   float y[8];
   Load8<T>::run(v + e, y);
   const float sc = s[row];
-  uint32_t lo = 0u, hi = 0u;
-  if (sc != 0.0f && !(scale_is_fast(sc) && enc8_div_fast(y, fast_rcp(sc), lo, hi))) {
-    lo = enc4_e4m3(qdiv(y[0], sc), qdiv(y[1], sc), qdiv(y[2], sc), qdiv(y[3], sc));
-    hi = enc4_e4m3(qdiv(y[4], sc), qdiv(y[5], sc), qdiv(y[6], sc), qdiv(y[7], sc));
-  }
+  uint32_t lo, hi;
+  quant8(y, sc, lo, hi);
   *reinterpret_cast<uint2*>(codes + (kTiled ? wtile_off(row, col, K) : e)) = make_uint2(lo, hi);
   if (kgm != nullptr && (col & (kGroup - 1)) == 0) kgm[(col / kGroup) * M + row] = sc;
 }

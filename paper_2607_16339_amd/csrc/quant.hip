@@ -127,7 +127,8 @@ __global__ __launch_bounds__(256, T <= 8 && !kAdd ? 4 : 1) void rmsnorm_quant_ke
     const int c = t * 64 + lane;
     const int cc = c < nchunk ? c : nchunk - 1;
     xv[t] = xr[cc];
-    wv[t] = wr[cc];
+    // (the row's other wavefronts' passes need no norm weight)
+    if (kRowScale || (t & ((1 << wpr_log2) - 1)) == part) wv[t] = wr[cc];
     if constexpr (kAdd) yv[t] = reinterpret_cast<const uint4*>(y + row * H)[cc];
   }
   if constexpr (kAdd) {  // the residual add, in registers (written back below)
@@ -136,7 +137,7 @@ __global__ __launch_bounds__(256, T <= 8 && !kAdd ? 4 : 1) void rmsnorm_quant_ke
       uint32_t* a = reinterpret_cast<uint32_t*>(&xv[t]);
       const uint32_t* b = reinterpret_cast<const uint32_t*>(&yv[t]);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) a[e] = pack_bf16x2(bf16lo(a[e]) + bf16lo(b[e]), bf16hi(a[e]) + bf16hi(b[e]));
+      for (int e = 0; e < 4; ++e) a[e] = cvt_pk_bf16(bf16lo(a[e]) + bf16lo(b[e]), bf16hi(a[e]) + bf16hi(b[e]));
     }
   }
 #pragma unroll
@@ -284,11 +285,11 @@ __global__ __launch_bounds__(256) void add_bf16_kernel(uint16_t* __restrict__ x,
     const uint32_t* pb = reinterpret_cast<const uint32_t*>(&b);
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-      pa[e] = pack_bf16x2(bf16lo(pa[e]) + bf16lo(pb[e]), bf16hi(pa[e]) + bf16hi(pb[e]));
+      pa[e] = cvt_pk_bf16(bf16lo(pa[e]) + bf16lo(pb[e]), bf16hi(pa[e]) + bf16hi(pb[e]));
     *reinterpret_cast<uint4*>(x + i8) = a;
   } else {
     for (int64_t i = i8; i < n; ++i)
-      x[i] = static_cast<uint16_t>(f32_to_bf16(bf16lo(x[i]) + bf16lo(y[i])));
+      x[i] = static_cast<uint16_t>(cvt_pk_bf16(bf16lo(x[i]) + bf16lo(y[i]), 0.0f));
   }
 }
 
