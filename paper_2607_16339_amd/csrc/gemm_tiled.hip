@@ -542,7 +542,7 @@ hipError_t launch_gateup_tiled(hipStream_t st, const uint8_t* xq, const float* x
   // 256 rows: M = 128 29 and 35 us (64 rows), 192 32 and 36 (96), 333 46 and 52
   // (192), 700 87 and 98 (192), 1536 138 and 160 (192).
   constexpr int kHeights[5] = {256, 192, 128, 96, 64};
-  constexpr double kGroup[5][2] = {{1.1, 0.73}, {0.92, 0.55}, {0.72, 0.36}, {0.57, 0.33}, {0.45, 0.35}};
+  constexpr double kGroup[5][2] = {{1.1, 0.73}, {0.92, 0.55}, {0.72, 0.36}, {0.57, 0.33}, {0.43, 0.34}};
   int pick = 0;
   double best = 0.0;
   for (int t = 0; t < 5; ++t) {
@@ -599,7 +599,12 @@ hipError_t launch_down_tiled(hipStream_t st, const uint8_t* hq, const float* hs,
     case 0: DN(256, 256); break;
     case 1: DN(128, 256); break;
     case 2: DN(128, 128); break;
-    default: DN(64, 128); break;
+    default:
+      if (col_s == nullptr && down_rows64_ok(M, H, I, ks))
+        e = launch_down_rows64(st, hq, hs, wq, ws, out, out_tap, part, M, H, I, ks);
+      else
+        DN(64, 128);
+      break;
   }
 #undef DN
   if (e != hipSuccess || ks == 1) return e;

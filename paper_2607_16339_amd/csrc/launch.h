@@ -80,6 +80,12 @@ hipError_t launch_down_tiled(hipStream_t st, const uint8_t* hq, const float* hs,
                              uint16_t* out, float* out_tap, int64_t M, int64_t H, int64_t I, void* ws_buf,
                              const float* col_s = nullptr);
 
+// Down GEMM on 64 x 128 tiles with the weights in registers: bit for bit the
+// tiled kernel's 64 x 128 tiles over ks K splits, for what down_rows64_ok accepts.
+bool down_rows64_ok(int64_t M, int64_t H, int64_t I, int ks);
+hipError_t launch_down_rows64(hipStream_t st, const uint8_t* hq, const float* hs, const uint8_t* wq, const float* ws,
+                              uint16_t* out, float* out_tap, float* part, int64_t M, int64_t H, int64_t I, int ks);
+
 // Skinny weight-streaming GEMMs (M <= kSkinnyMaxM; skinny_supported() also
 // checks that the activation rows fit the gate/up kernel's LDS).
 // The gate/up stage needs an fp32 scratch buffer of skinny_gateup_ws_bytes()

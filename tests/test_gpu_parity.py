@@ -450,6 +450,24 @@ def test_skinny_slab_pairs_per_workgroup(M, H, I):
     check_gateup_model(host(t["xq"]), host(t["xs"]), wgu_q, wgu_s, I, host(t["h_tap"]), host(t["hq"]), host(t["hs"]))
 
 
+@pytest.mark.parametrize("M,H,I", [(65, 128, 128), (100, 384, 768), (128, 256, 16384), (129, 512, 1536),
+                                   (200, 1024, 4224), (1000, 512, 1920)])
+def test_down_rows_of_64(M, H, I):
+    """The down GEMM with its weights in registers: one K-group, K-group counts
+    that leave 1, 2, 3 and all of the last chunk of 4, 8 K splits and 2 of unequal
+    length, last row tiles of 1, 8, 36, 40 and 64 rows, up to 16 row tiles."""
+    _say("down rows64 M=%d H=%d I=%d" % (M, H, I))
+    lc.lacache_set_path_policy(2)
+    w = synth.Workload(93, "rows64", M, H, I, act="outlier", outlier_ratio=0.02)
+    lay = Layer(w, layer=1)
+    xb = synth.make_x(w, layer=1)
+    t = run_stages(dev_bf16(xb), lay, M, H, I)
+    wgu_q, wgu_s, wd_q, wd_s = lay.host_weights()
+    check_requant_exact(host(t["h_tap"]), host(t["hq"]), host(t["hs"]))
+    check_down_same_operands(host(t["hq"]), host(t["hs"]), wd_q, wd_s, host(t["out_tap"]), host_bf16(t["out"]))
+    check_down_model(host(t["hq"]), host(t["hs"]), wd_q, wd_s, host(t["out_tap"]))
+
+
 def _full_size_case(big_layer, w, step, rows_pick, policy):
     lc.lacache_set_path_policy(policy)
     xb = synth.make_x(w, layer=1, step=step)
