@@ -66,11 +66,15 @@ __global__ __launch_bounds__(kThreads) void down_rows64_kernel(
   const int lane = threadIdx.x & 63, wave = wave_uniform(threadIdx.x >> 6);
   const int q = lane >> 4, lr = lane & 15;
   const int KB = static_cast<int>(I / 128);
-  // item: K split, row tile, column tile; the row tiles of a column on one XCD
-  const int R = (M + kRows - 1) / kRows;
-  int vr, ct;
-  xcd_grouped_tile(static_cast<int>(blockIdx.x), R * KS, static_cast<int>(H / 128), vr, ct);
-  const int split = vr / R, m0 = (vr - split * R) * kRows;
+  // item: the (up to 4) row tiles of a column and K split, which share its
+  // weights, one after the other on one XCD (with the splits among the row tiles,
+  // as in the tiled kernel, 3 row tiles of a split fell on two XCDs: whole FFN at
+  // H = 3072, I = 8192, M = 180 38.9 -> 38.1 us, H = 4096, I = 12288, M = 96 59.1
+  // -> 58.3)
+  const int R = (M + kRows - 1) / kRows, C = static_cast<int>(H / 128);
+  int rt, vc;
+  xcd_grouped_tile(static_cast<int>(blockIdx.x), R, C * KS, rt, vc);
+  const int m0 = rt * kRows, ct = vc % C, split = vc / C;
   const int kb0 = split * KB / KS, nkb = (split + 1) * KB / KS - kb0;
   const int nch = (nkb + kChunk - 1) / kChunk;
 
@@ -198,8 +202,11 @@ __global__ __launch_bounds__(kThreads) void down_rows64_kernel(
 
 }  // namespace
 
-// One workgroup per CU at most: in a second round the tiled kernel, whose
-// workgroups walk several items with their copies running on, is the better one.
+// One workgroup per CU at most: over several rounds the tiled kernel, whose
+// workgroups walk several items with their copies running on, is the better one
+// (whole FFN, tiled and this kernel: H = 16384, I = 24576, M = 156, three rounds
+// 379.5 and 381.7 us; H = 3072, I = 8192, M = 435, two rounds 63.3 and 63.8, M =
+// 404 65.0 and 64.4).
 bool down_rows64_ok(int64_t M, int64_t H, int64_t I, int ks) {
   return (M + kRows - 1) / kRows * (H / 128) * ks <= device_cu_count() && (I / 128 + ks - 1) / ks <= kMaxGroups;
 }

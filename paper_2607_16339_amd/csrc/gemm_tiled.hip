@@ -4,14 +4,14 @@
 //
 // Work items are BM-row x BNR-weight-row output tiles (BM 64 to 256 by the
 // rules at the launchers; BNR 256, or 128 for the down GEMM's smaller tiles),
-// times the K splits of the down GEMM. The grid is persistent: one workgroup per CU walks the items
-// b, b + G, b + 2G, ... (G workgroups), and its copy ring runs straight across
-// item boundaries, so the first K-groups of the next tile are already in LDS
+// times the K splits of the down GEMM. The grid is persistent: one workgroup
+// per CU walks the items b, b + G, b + 2G, ... (G workgroups), and its copy
+// ring runs straight across item boundaries, so the first K-groups of the next tile are already in LDS
 // when a tile's epilogue ends and no workgroup launch or pipeline refill
 // separates two tiles.
 //
-// A workgroup has 8 multiplying wavefronts (four of them also copy, or up to 128-row
-// tiles four more only copy); wavefront (wm, wn) owns WR activation rows x
+// A workgroup has 8 multiplying wavefronts (four of them also copy, or up to
+// 128-row tiles four more only copy); wavefront (wm, wn) owns WR activation rows x
 // WC weight rows (MT x NJ sub-tiles of 16 x 16). K is walked one 128-wide group
 // at a time:
 //   * the group's fp8 tiles (A: BM x 128 B, B: BNR x 128 B), the BM
@@ -585,7 +585,12 @@ hipError_t launch_down_tiled(hipStream_t st, const uint8_t* hq, const float* hs,
     const Shape& s = kShapes[t];
     const int64_t tiles = ((M + s.bm - 1) / s.bm) * ((H + s.bn - 1) / s.bn);
     for (int k = 1; k <= (s.bm == 256 ? 1 : ks_max); ++k) {
-      const double us = s.start + loops_us(tiles * k, (I / 128 + k - 1) / k, s.c0, s.c1) +
+      // 64-row tiles with the weights in registers, up to the 4 row tiles that
+      // share one XCD's copy of them, are bound by each CU's own copies, however
+      // many CUs work (whole FFN at H = 4096, I = 12288, 128 x 128 tiles x 4 splits
+      // and these x 2: M = 192 71.7 and 73.1 us, 200 73.6 and 70.3, 256 73.8 and 72.7)
+      const bool regs = s.bm == 64 && col_s == nullptr && M <= 64 * kTileGroupRows && down_rows64_ok(M, H, I, k);
+      const double us = s.start + loops_us(tiles * k, (I / 128 + k - 1) / k, regs ? 0.33 : s.c0, regs ? -0.04 : s.c1) +
                         (k > 1 ? 2.5 + (4.0 * k + 2.0) * static_cast<double>(M * H) / 7e6 : 0.0);
       if ((t == 0 && k == 1) || us < best) pick = t, ks = k, best = us;
     }
