@@ -147,10 +147,11 @@ int lacache_add_rmsnorm_quant(void* stream, uint16_t* resid, const uint16_t* y, 
  * acc[m,n] = sum_kb (xs[kb,m] * wgu_s[n/128,kb]) * dot_kb(xq[m,:], wgu_q[n,:])
  * accumulated in fp32; h = SiLU(acc[:, j]) * acc[:, I + j].
  * On the skinny path h passes through the library workspace (M x I fp32),
- * and the K range is split into four parts whose fp32 partial sums are
- * added in part order; at 33..64 rows the K range is first split into two
- * halves (separate workgroups) whose gate and up sums pass through the
- * workspace and are added in half order before SwiGLU.
+ * and the K range is split into 4, 6 or 12 parts (by I) whose fp32 partial
+ * sums are added in part order. At 33..64 rows whose codes over all of K do
+ * not fit the LDS, the K range is first split into two halves (separate
+ * workgroups, 2 parts each) whose gate and up sums pass through the workspace
+ * and are added in half order before SwiGLU.
  */
 int lacache_gateup_swiglu_quant(void* stream, const uint8_t* xq, const float* xs, const uint8_t* wgu_q,
                                 const float* wgu_s, uint8_t* hq, float* hs, float* h_tap,
@@ -163,9 +164,10 @@ int lacache_gateup_swiglu_quant(void* stream, const uint8_t* xq, const float* xs
  *   out     [M x H] bf16, rounded to nearest-even from fp32         (output)
  *   out_tap [M x H] fp32 or NULL: if non-NULL, also receives the fp32 value
  *           that was rounded (test hook)
- * On the skinny path (M <= 64) the K range is split over the four
+ * On the skinny path (M <= 64) the K range is split over the 4 or 8
  * wavefronts of a workgroup, whose fp32 partial sums are added in wavefront
- * order.
+ * order. On the tiled path it may be split over several workgroups, whose
+ * partial sums pass through the workspace and are added in split order.
  */
 int lacache_down_proj(void* stream, const uint8_t* hq, const float* hs, const uint8_t* wd_q, const float* wd_s,
                       uint16_t* out, float* out_tap, int64_t M, int64_t H, int64_t I, int group);
@@ -391,8 +393,8 @@ int lacache_embed_rmsnorm(void* stream, const int32_t* token_ids, const int32_t*
  * accumulation (bf16 MFMAs; the K range is split over four partial sums added
  * in a fixed order); out_tap (nullable) receives the fp32 result. Up to 128
  * rows W is streamed from HBM once per 64 rows of a (the few rows of a block);
- * above, 128-row output tiles read it once per 128 rows. Both give every row
- * the same bytes, so a row's result does not depend on M. */
+ * above, output tiles of 128 or 256 rows read it once per tile. All give every
+ * row the same bytes, so a row's result does not depend on M. */
 int lacache_linear_bf16(void* stream, const uint16_t* a, const uint16_t* w, uint16_t* out, float* out_tap, int64_t M,
                         int64_t N, int64_t K);
 
@@ -409,7 +411,8 @@ int lacache_rope_scatter(void* stream, const uint16_t* qkv, const int32_t* rows,
                          const float* rope_sin, uint16_t* q, uint16_t* k, uint16_t* v, int64_t heads, int64_t N);
 
 /* The three steps above in one call (embedding + norm, the QKV projection
- * with w_qkv [3 heads 128 x H] bf16, RoPE + scatter), with a library-owned
+ * with w_qkv [3 heads 128 x H] bf16, RoPE + scatter in the projection's
+ * epilogue; the same bytes as the three calls), with a library-owned
  * workspace of lacache_first_layer_workspace_bytes(R, heads, H) bytes. */
 int lacache_first_layer_tokens(void* stream, const int32_t* token_ids, const int32_t* rows, int64_t R,
                                const uint16_t* embed, int64_t vocab, const uint16_t* norm_w, const uint16_t* w_qkv,
@@ -420,9 +423,9 @@ size_t lacache_first_layer_workspace_bytes(int64_t R, int64_t heads, int64_t H);
 /*
  * Kernel-path policy for the GEMM stages, process-wide:
  *   0 = automatic (the skinny weight-streaming kernels for M <= 64 whose
- *       activation rows fit the gate/up kernel's LDS: ceil(M/16) 16 (H + 16)
- *       <= 132096 bytes for M <= 32, ceil(M/16) 16 (ceil(H/256) 128 + 16)
- *       <= 132096 for 33..64 rows; H <= 8192, I <= 16384; the tiled MFMA
+ *       activation rows fit the gate/up kernel's LDS, over all of K (ceil(M/16)
+ *       16 (H + 16) <= 132096 bytes) or, for 33..64 rows, over half of it
+ *       (ceil(M/16) 16 (ceil(H/256) 128 + 16) <= 132096); H <= 8192, I <= 16384; the tiled MFMA
  *       kernels otherwise), 1 = always skinny (other shapes return
  *       LACACHE_ERR_UNSUPPORTED), 2 = always tiled.
  * Returns the previous policy, or LACACHE_ERR_INVALID_ARG for other values.

@@ -19,7 +19,8 @@
 //                         128 x 192 or 256 x 192 output tiles;
 //   rope_scatter_kernel   rotate-half RoPE of the Q and K heads from fp32 cos /
 //                         sin tables, V unrotated, scattered to each row's
-//                         position in Q, K, V.
+//                         position in Q, K, V, as a stage of its own; the whole
+//                         call does the same in the projection's epilogue.
 // Token ids outside [0, vocab) and row indices outside [0, N) are skipped on
 // the device (no access is made for them).
 #include <type_traits>

@@ -10,8 +10,9 @@
 //          wavefront each), P = 1, 2 or 3 by I, or 6 x 2 where it takes one
 //          half of K. The activation codes are copied into LDS once per
 //          workgroup (over all of K where they fit, else, at 33..64 rows,
-//          over one half of K, the halves in two workgroups); the weights go global -> VGPRs with non-temporal
-//          16-byte loads straight into the MFMA operand layout, a ring of
+//          over one half of K, the halves in two workgroups); the weights go
+//          global -> VGPRs with non-temporal 16-byte loads straight into the
+//          MFMA operand layout, a ring of
 //          K-groups per wavefront in straight-line code (the compiler waits
 //          for one K-group's registers at a time). The weight tile layout
 //          (wtile_off) makes each load read 1 KB contiguous; on a row-major
@@ -19,8 +20,8 @@
 //          which streams about 25 % slower on gfx950. SwiGLU after the
 //          partials are added; h stored as fp32 (K halves: the gate and
 //          up sums of each K half, added by the second kernel before
-//          SwiGLU). A second kernel quantizes h per 1x128 group (a group's columns come from several workgroups,
-//          and stream order is the cheapest way to make all of them visible:
+//          SwiGLU). A second kernel quantizes h per 1x128 group (a group's
+//          columns come from several workgroups, and stream order is the cheapest way to make all of them visible:
 //          device-scope fences inside the kernel cost more than the stream).
 // down:    16 output columns per workgroup, 8 K parts (up to 32 rows and 96
 //          K-groups) or 4, direct-to-LDS copies of both operands (see the
@@ -59,13 +60,13 @@ __device__ __forceinline__ v8i cat_frag(u4v lo, u4v hi) {
 }
 
 // gate/up: a workgroup owns PAIRS (gate, up) slab pairs; each pair's K
-// range is split into KQ parts, one wavefront each (PAIRS KQ = 12). The workgroup first
-// loads the M activation rows (codes) of its K range into LDS, rows padded by
+// range is split into KQ parts, one wavefront each (PAIRS KQ = 12). The
+// workgroup first loads the M activation rows (codes) of its K range into LDS, rows padded by
 // 16 bytes so that the 16 rows of an operand read fall on 16 different bank
 // groups; then every wavefront streams its 32 weight rows over its K part.
 // The KQ fp32 partials meet in LDS and are added in part order.
 // NH = 1: the workgroup covers all of K and applies SwiGLU (h to hbuf).
-// NH = 2 (33..64 rows, whose codes over all of K do not fit the LDS): the
+// NH = 2 (33..64 rows, where their codes over all of K do not fit the LDS): the
 // workgroups of blockIdx.y = 0, 1 cover the two halves of K and store their
 // gate and up sums to part[y] [M][2I]; the h-quantization kernel adds the two
 // halves in that order and applies SwiGLU.
@@ -507,9 +508,9 @@ __global__ __launch_bounds__(256) void skinny_hquant2_kernel(const float* __rest
   }
 }
 
-// Shapes the kernels cover: M <= 32 activation rows over all of K (NH = 1),
-// or 33..64 rows over half of K (NH = 2), that fit the gate/up kernel's LDS
-// and scale tables; down: K parts that fit its scale tables.
+// Shapes the kernels cover: activation rows that fit the gate/up kernel's LDS
+// and scale tables over all of K (NH = 1) or, for 33..64 rows, over half of it
+// (NH = 2); down: K parts that fit its scale tables.
 bool gateup_fits(int64_t R, int64_t kbw) { return R * (kbw * 128 + 16) <= kVuXBytes && kbw * R <= kVuScales; }
 // K pieces: 1, or 2 where 33..64 rows over all of K do not fit (one piece needs
 // no partial sums in memory: 64 rows at H = 2048, I = 6144 31.9 -> 27.8 us)
