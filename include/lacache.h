@@ -147,11 +147,11 @@ int lacache_add_rmsnorm_quant(void* stream, uint16_t* resid, const uint16_t* y, 
  * acc[m,n] = sum_kb (xs[kb,m] * wgu_s[n/128,kb]) * dot_kb(xq[m,:], wgu_q[n,:])
  * accumulated in fp32; h = SiLU(acc[:, j]) * acc[:, I + j].
  * On the skinny path h passes through the library workspace (M x I fp32),
- * and the K range is split into 4, 6 or 12 parts (by I) whose fp32 partial
- * sums are added in part order. At 33..64 rows whose codes over all of K do
- * not fit the LDS, the K range is first split into two halves (separate
- * workgroups, 2 parts each) whose gate and up sums pass through the workspace
- * and are added in half order before SwiGLU.
+ * and the K range is split into four parts whose fp32 partial sums are added
+ * in part order, at 33..64 rows as (p0 + p1) + (p2 + p3): the two halves of K
+ * are separate workgroups there where the codes over all of K do not fit the
+ * LDS, and their gate and up sums pass through the workspace. A row's h depends
+ * on M only through these two orders, and not on I.
  */
 int lacache_gateup_swiglu_quant(void* stream, const uint8_t* xq, const float* xs, const uint8_t* wgu_q,
                                 const float* wgu_s, uint8_t* hq, float* hs, float* h_tap,

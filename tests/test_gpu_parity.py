@@ -433,9 +433,9 @@ def test_skinny_k_parts(M, H, I):
 @pytest.mark.parametrize("M,H,I", [(5, 384, 4224), (48, 2560, 4224), (20, 256, 8320), (33, 128, 8192),
                                    (64, 2048, 128), (64, 2176, 256)])
 def test_skinny_slab_pairs_per_workgroup(M, H, I):
-    """The gate/up kernel's other workgroup shapes: 2 slab pairs x 6 K parts
+    """The gate/up kernel's other workgroup shapes: 2 slab pairs x 4 K parts
     (I = 4224, 8192), 3 x 4 with a partial last workgroup (I = 8320) and 1 x
-    12 (I = 128, 256), at 33..64 rows with all of K in the LDS up to its
+    4 (I = 128, 256), at 33..64 rows with all of K in the LDS up to its
     largest (H = 2560 at 48 rows, 2048 at 64) and with two K halves just above
     (2176 at 64)."""
     _say("skinny pairs M=%d H=%d I=%d" % (M, H, I))
@@ -448,6 +448,51 @@ def test_skinny_slab_pairs_per_workgroup(M, H, I):
     check_norm_exact(xb, lay.bits["norm_w"], host(t["xq"]), host(t["xs"]))
     check_requant_exact(host(t["h_tap"]), host(t["hq"]), host(t["hs"]))
     check_gateup_model(host(t["xq"]), host(t["xs"]), wgu_q, wgu_s, I, host(t["h_tap"]), host(t["hq"]), host(t["hs"]))
+
+
+@pytest.mark.parametrize("M,H", [(5, 640), (32, 2048), (33, 640), (64, 2048)])
+def test_skinny_gateup_does_not_depend_on_i(M, H):
+    """An element's four K parts and the order they are walked and added in do
+    not depend on how many slab pairs share a workgroup (1 at I = 384, 2 at
+    4224, 3 at 8448): the same weight rows give the same bytes."""
+    _say("skinny gate/up of several I, M=%d H=%d" % (M, H))
+    lc.lacache_set_path_policy(1)
+    wide = 8448
+    w = synth.Workload(91, "narrow", M, H, wide, act="outlier", outlier_ratio=0.02)
+    lay = Layer(w, layer=1)
+    xq = torch.empty((M, H), dtype=torch.uint8, device=DEV)
+    xs = torch.empty((H // 128, M), dtype=torch.float32, device=DEV)
+    lc.lacache_rmsnorm_quant(dev_bf16(synth.make_x(w, layer=1)), lay.norm_w, xq, xs)
+    gu = dev_bf16(np.concatenate([lay.bits["w_gate"], lay.bits["w_up"]]))
+    ref = None
+    for I in (wide, 4224, 384):
+        wq, ws = lc.quantize_weights(torch.cat([gu[:I], gu[wide:wide + I]]).contiguous())
+        hq = torch.full((M, I), 0xFF, dtype=torch.uint8, device=DEV)
+        hs = torch.full((I // 128, M), float("nan"), dtype=torch.float32, device=DEV)
+        tap = torch.full((M, I), float("nan"), dtype=torch.float32, device=DEV)
+        lc.lacache_gateup_swiglu_quant(xq, xs, wq, ws, hq, hs, tap)
+        torch.cuda.synchronize()
+        if ref is None:
+            ref = (hq, hs, tap)
+        assert torch.equal(tap.view(torch.int32), ref[2][:, :I].contiguous().view(torch.int32)), I
+        assert torch.equal(hq, ref[0][:, :I]), I
+        assert torch.equal(hs.view(torch.int32), ref[1][:I // 128].view(torch.int32)), I
+
+
+def test_skinny_gateup_of_one_and_two_k_pieces():
+    """33..64 rows: all of K in one workgroup (48 rows at H = 2560) and two K
+    halves (64 rows) add an element's K parts in the same order."""
+    H, I = 2560, 384
+    lc.lacache_set_path_policy(1)
+    w = synth.Workload(91, "pieces", 64, H, I, act="outlier", outlier_ratio=0.02)
+    lay = Layer(w, layer=1)
+    x = dev_bf16(synth.make_x(w, layer=1))
+    taps = []
+    for M in (48, 64):
+        _say("skinny gate/up M=%d H=%d" % (M, H))
+        taps.append(run_stages(x[:M].contiguous(), lay, M, H, I)["h_tap"])
+    torch.cuda.synchronize()
+    assert torch.equal(taps[0].view(torch.int32), taps[1][:48].view(torch.int32))
 
 
 @pytest.mark.parametrize("M,H,I", [(65, 128, 128), (100, 384, 768), (128, 256, 16384), (129, 512, 1536),
