@@ -270,7 +270,9 @@ int lacache_encode_e4m3(void* stream, const float* v, uint8_t* codes, int64_t n)
  *   mode 1  resume: query blocks inside U load their cached state and scan
  *           only the key blocks that overlap C; the result equals plain
  *           attention of the current inputs when, since the mode-0 call with
- *           the same c_begin, c_end, only rows of C of q, k and v changed;
+ *           the same c_begin, c_end, only rows of C of q, k and v changed, bit
+ *           for bit, whatever the head counts of the calls (a head's result
+ *           does not depend on the other heads of its call);
  *   mode 2  plain attention; the cache pointers are not used (may be NULL).
  * d must be 128 and N a multiple of 64 (LACACHE_ERR_UNSUPPORTED otherwise);
  * heads <= 4096, N <= 2^20; 0 <= c_begin <= c_end <= N, mode in 0..2

@@ -1,7 +1,6 @@
 // First-layer FlashAttention with FACache (Sec. 3.3, FACache; Eqs. 2-6).
 //
-// Work decomposition. A workgroup of W wavefronts (or two such groups, which
-// share the key blocks inside U between them) owns 32 query rows per
+// Work decomposition. A workgroup of W wavefronts owns 32 query rows per
 // wavefront (32 W rows) of one head and streams 64-key tiles of K and V
 // through an S-stage LDS ring filled by direct global->LDS copies, so the
 // copies of the next S - 1 tiles overlap the MFMAs of the current one.
@@ -100,20 +99,13 @@ __device__ __forceinline__ int heavy_first(int lo, int s, int n, int nqb, int nh
   return (gl / nl) * nqb + nh + gl % nl;
 }
 
-// kMode 0: populate, 1: resume, 2: plain attention; W wavefronts, S stages;
-// NG groups of W wavefronts: with NG = 2 the second group takes every other key
-// block inside U of the same query rows, on a ring of its own, and hands its
-// state over before the blocks overlapping C (a short call: see launch_facache_attention)
-template <int kMode, int W, int S, int NG>
-__global__ __launch_bounds__(64 * W * NG, 2) void facache_attention_kernel(AttnArgs a) {
-  static_assert(NG == 1 || (W == 4 && S * kStageBytes >= W * 64 * 256), "the second ring holds the exchanged state");
-  __shared__ __align__(16) uint8_t smem_all[NG][S * kStageBytes];
-  __shared__ float ex_ml[NG == 1 ? 1 : W * 64 * 2];
+// kMode 0: populate, 1: resume, 2: plain attention; W wavefronts, S stages
+template <int kMode, int W, int S>
+__global__ __launch_bounds__(64 * W, 2) void facache_attention_kernel(AttnArgs a) {
+  __shared__ __align__(16) uint8_t smem[S * kStageBytes];
   constexpr int QR = kQR, WR = W * QR;
   constexpr int kPer = 2 * 1024 / (64 * W);  // copies per thread per tile
-  const int t = threadIdx.x & (64 * W - 1), lane = t & 63, wave = wave_uniform(t >> 6);
-  const int grp = NG == 1 ? 0 : wave_uniform(threadIdx.x / (64 * W));
-  uint8_t* smem = smem_all[grp];
+  const int t = threadIdx.x, lane = t & 63, wave = wave_uniform(t >> 6);
   const int g = lane >> 5, r = lane & 31;
 
   // work item: consecutive items on one XCD (resume: the chunk's heavy items first)
@@ -133,12 +125,9 @@ __global__ __launch_bounds__(64 * W * NG, 2) void facache_attention_kernel(AttnA
   const bool use_cache = kMode == 1 && in_u;  // this wavefront resumes from the cache
   const bool light = kMode == 1 && !heavy;     // ... and so does every wavefront of the workgroup
   const int nU = a.nkb - a.nc;
-  // this group's list: its key blocks inside U (with NG = 2 the group's share),
-  // then (the first group) those overlapping C
-  const int nu = light ? 0 : (nU + NG - 1 - grp) / NG;  // of this group
-  const int nu0 = light ? 0 : (nU + NG - 1) / NG;       // of the first group (the more)
-  const int nlist = nu + (grp == 0 ? a.nc : 0);
-  const int nsteps = nu0 + a.nc;
+  // the list: the key blocks inside U, then those overlapping C
+  const int nu = light ? 0 : nU;
+  const int nlist = nu + a.nc;
   const int64_t hN = h * a.N;
   const uint16_t* kh = a.k + hN * kD;
   const uint16_t* vh = a.v + hN * kD;
@@ -155,7 +144,7 @@ __global__ __launch_bounds__(64 * W * NG, 2) void facache_attention_kernel(AttnA
   for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
     for (int e = 0; e < 16; ++e) ot[dt][e] = 0.0f;
-  if (use_cache && valid && grp == 0) {
+  if (use_cache && valid) {
     m = a.cm[sb];
     l = g == 0 ? a.cl[sb] : 0.0f;
 #pragma unroll
@@ -173,8 +162,7 @@ __global__ __launch_bounds__(64 * W * NG, 2) void facache_attention_kernel(AttnA
   // i-th key block of this workgroup's list
   auto key_block = [&](int i) -> int {
     if (i >= nu) return a.cb0 + (i - nu);
-    const int u = i * NG + grp;
-    return u < a.cb0 ? u : u + a.nc;
+    return i < a.cb0 ? i : i + a.nc;
   };
   // Copy K and V tiles of list entry i into stage s. LDS slot p (16 bytes)
   // holds key p / 16, 16-byte chunk (p % 16) ^ swizzle(key): K swizzles by
@@ -299,7 +287,7 @@ __global__ __launch_bounds__(64 * W * NG, 2) void facache_attention_kernel(AttnA
 #pragma unroll
   for (int i = 0; i < S - 1; ++i)
     if (i < nlist) issue(i, i);
-  for (int i = 0; i < nsteps; ++i) {
+  for (int i = 0; i < nlist; ++i) {
     // this thread's copies of tile i have landed (those of the next S - 2 may be in flight) ...
     if (i + S - 2 < nlist)
       wait_vm<(S - 2) * kPer>();
@@ -308,8 +296,8 @@ __global__ __launch_bounds__(64 * W * NG, 2) void facache_attention_kernel(AttnA
     bar();  // ... and everyone's have; everyone is done reading the stage refilled next
     const int next = i + S - 1 < nlist ? i + S - 1 : -1;
     // a resuming wavefront skips the U blocks
-    const bool work = valid && (NG == 1 || i < nlist) && !(use_cache && i < nu0);
-    if (kMode == 1 && NG == 1) {
+    const bool work = valid && !(use_cache && i < nu);
+    if (kMode == 1) {
       // (most items of a large resume load their state and stream one tile)
       if (next >= 0) issue(next, (i + S - 1) % S);
       if (work) compute(i % S, -1, 0);
@@ -318,45 +306,9 @@ __global__ __launch_bounds__(64 * W * NG, 2) void facache_attention_kernel(AttnA
     } else if (next >= 0) {
       issue(next, (i + S - 1) % S);
     }
-    if (!light && i == nu0 - 1) {
+    if (!light && i == nu - 1) {
       merge_l();
-      if constexpr (NG == 2) {
-        // the second group's state joins the first's, through its own ring,
-        // which is idle from here on (the first group's holds the next tile)
-        if (nU > 1) {
-          float4* ex = reinterpret_cast<float4*>(smem_all[1]) + wave * 16 * 64 + lane;
-          bar();  // every wavefront of the second group has read its last tile
-          if (grp == 1) {
-#pragma unroll
-            for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-              for (int b = 0; b < 4; ++b)
-                ex[(4 * dt + b) * 64] = make_float4(ot[dt][4 * b], ot[dt][4 * b + 1], ot[dt][4 * b + 2], ot[dt][4 * b + 3]);
-            ex_ml[t] = m;
-            ex_ml[64 * W + t] = l;
-          }
-          asm volatile("" ::: "memory");
-          wait_lds();
-          bar();
-          if (grp == 0 && valid && !use_cache) {
-            const float m1 = ex_ml[t], l1 = ex_ml[64 * W + t], mn = __builtin_fmaxf(m, m1);
-            const float a0 = __builtin_amdgcn_exp2f(m - mn), a1 = __builtin_amdgcn_exp2f(m1 - mn);
-            m = mn;
-            l = __builtin_fmaf(a0, l, a1 * l1);
-#pragma unroll
-            for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-              for (int b = 0; b < 4; ++b) {
-                const float4 o1 = ex[(4 * dt + b) * 64];
-                ot[dt][4 * b + 0] = __builtin_fmaf(a0, ot[dt][4 * b + 0], a1 * o1.x);
-                ot[dt][4 * b + 1] = __builtin_fmaf(a0, ot[dt][4 * b + 1], a1 * o1.y);
-                ot[dt][4 * b + 2] = __builtin_fmaf(a0, ot[dt][4 * b + 2], a1 * o1.z);
-                ot[dt][4 * b + 3] = __builtin_fmaf(a0, ot[dt][4 * b + 3], a1 * o1.w);
-              }
-          }
-        }
-      }
-      if (kMode == 0 && in_u && valid && grp == 0) {
+      if (kMode == 0 && in_u && valid) {
         if (g == 0) {
           a.cm[sb] = m;
           a.cl[sb] = l;
@@ -371,7 +323,7 @@ __global__ __launch_bounds__(64 * W * NG, 2) void facache_attention_kernel(AttnA
     }
   }
 
-  if (!valid || grp != 0) return;
+  if (!valid) return;
   const float lt = l + __shfl_xor(l, 32, 64);
   const float inv = 1.0f / lt;
 #pragma unroll
@@ -384,7 +336,7 @@ __global__ __launch_bounds__(64 * W * NG, 2) void facache_attention_kernel(AttnA
   if (a.lse != nullptr && g == 0) a.lse[sb] = (m + __log2f(lt)) * 0.69314718055994531f;
 }
 
-template <int W, int S, int NG>
+template <int W, int S>
 hipError_t launch_ws(hipStream_t st, AttnArgs a, int64_t heads, int mode) {
   constexpr int WR = W * kQR;
   a.nqb = static_cast<int>((a.N + WR - 1) / WR);
@@ -395,13 +347,13 @@ hipError_t launch_ws(hipStream_t st, AttnArgs a, int64_t heads, int mode) {
   // workgroups per CU): in a single round every item starts at once and the
   // order only decides which items share a CU
   a.heavy_first = a.total > 2 * device_cu_count() ? 1 : 0;
-  const dim3 grid(static_cast<unsigned>(a.total)), block(64 * W * NG);
+  const dim3 grid(static_cast<unsigned>(a.total)), block(64 * W);
   if (mode == 0)
-    hipLaunchKernelGGL((facache_attention_kernel<0, W, S, NG>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((facache_attention_kernel<0, W, S>), grid, block, 0, st, a);
   else if (mode == 1)
-    hipLaunchKernelGGL((facache_attention_kernel<1, W, S, NG>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((facache_attention_kernel<1, W, S>), grid, block, 0, st, a);
   else
-    hipLaunchKernelGGL((facache_attention_kernel<2, W, S, NG>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((facache_attention_kernel<2, W, S>), grid, block, 0, st, a);
   return hipGetLastError();
 }
 
@@ -426,15 +378,13 @@ hipError_t launch_facache_attention(hipStream_t st, const uint16_t* q, const uin
     a.nc = static_cast<int>((c1 + kKB - 1) / kKB) - a.cb0;
   }
   a.scale_log2 = 1.4426950408889634f / 11.313708498984761f;  // log2(e) / sqrt(128)
-  // Calls of at most one workgroup per CU are bound by a workgroup's chain of
-  // key blocks, with one wavefront per SIMD: two groups of wavefronts shorten it
-  // from 12 key blocks on (4 x 2048 plain 43.6 -> 37.6 us, 32 x 1024 resume 27.9 ->
-  // 25.6; at 8 blocks the exchange costs what it saves: 32 x 512 plain 16.2 ->
-  // 16.5). The rule looks at the shape alone, so that the three modes of a
-  // call agree bit for bit.
-  if (heads * ((N + 4 * kQR - 1) / (4 * kQR)) <= device_cu_count() && a.nkb >= 12)
-    return launch_ws<4, 2, 2>(st, a, heads, mode);
-  return launch_ws<4, 2, 1>(st, a, heads, mode);
+  // Every call takes the same order, so that a row's state and output depend on N
+  // and C alone and a cache serves calls of any head count bit for bit. (Calls of
+  // at most one workgroup per CU are bound by a workgroup's chain of key blocks;
+  // two groups of wavefronts that shared the blocks inside U took 35.2 us instead
+  // of 43.3 at 4 x 2048 plain, with another running maximum under P's rounding:
+  // 5.6e-4 of o away from the other calls.)
+  return launch_ws<4, 2>(st, a, heads, mode);
 }
 
 }  // namespace lacache

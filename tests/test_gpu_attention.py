@@ -167,15 +167,14 @@ def test_single_block_and_extreme_scores():
 
 @pytest.mark.parametrize("N,c0,c1", [(832, 100, 132), (768, 0, 64), (832, 700, 832), (832, 0, 832), (832, 64, 832),
                                      (832, 0, 704), (768, 5, 5)])
-def test_key_blocks_shared_by_two_groups(N, c0, c1):
-    """Short calls of 12 and more key blocks (2 heads): the blocks inside U are
-    shared by two groups of wavefronts, odd and even counts, one block, none,
-    all of them; half a workgroup of rows past the end (N = 832). Every mode
-    against the oracle, and the three bit for bit."""
+def test_key_blocks_of_few_heads(N, c0, c1):
+    """Few heads and 12 or 13 key blocks, odd and even counts of them inside U,
+    one block, none, all of them; half a workgroup of rows past the end (N =
+    832). Every mode against the oracle, and the three bit for bit."""
     rng = np.random.default_rng(N + c0 + c1)
     q, k, v = (synth.to_bf16_bits(rng.standard_normal((2, N, 128)).astype(np.float32) * s) for s in (1.5, 1.5, 1.0))
     r = Run(q, k, v)
-    _say("two groups N=%d C=[%d,%d)" % (N, c0, c1))
+    _say("few heads N=%d C=[%d,%d)" % (N, c0, c1))
     plain = r(c0, c1, 2)
     _check_close(plain, A.attention(q, k, v), v, "plain")
     assert _bits_equal(r(c0, c1, 0), plain)
@@ -185,6 +184,31 @@ def test_key_blocks_shared_by_two_groups(N, c0, c1):
             x[:, c0:c1] = synth.to_bf16_bits(rng.standard_normal((2, c1 - c0, 128)).astype(np.float32))
         r.set_inputs(q, k, v)
         assert _bits_equal(r(c0, c1, 1), r(c0, c1, 2))
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+def test_cache_is_shared_between_calls_of_other_head_counts(mode):
+    """A cache populated for 256 heads of 1024 tokens, resumed for one 2-head
+    sequence of them (and the other way round): the plain attention's bits, in
+    a call of either size. A row's arithmetic depends on N and C alone."""
+    heads, N, c0, c1 = 256, 1024, 544, 576
+    rng = np.random.default_rng(mode)
+    q, k, v = (synth.to_bf16_bits(rng.standard_normal((heads, N, 128), dtype=np.float32) * np.float32(s))
+               for s in (1.5, 1.5, 1.0))
+    big, small = Run(q, k, v), Run(q[:2], k[:2], v[:2])
+    first, then = (big, small) if mode == 0 else (small, big)
+    _say("cache of %d heads resumed for %d" % (first.heads, then.heads))
+    first(c0, c1, 0)
+    for a, b in ((first.cm, then.cm), (first.cl, then.cl), (first.co, then.co)):
+        b[:2].copy_(a[:2])
+    new = [synth.to_bf16_bits(rng.standard_normal((2, c1 - c0, 128), dtype=np.float32)) for _ in range(3)]
+    for x, n in zip((q, k, v), new):
+        x[:2, c0:c1] = n
+    big.set_inputs(q, k, v)
+    small.set_inputs(q[:2], k[:2], v[:2])
+    res = then(c0, c1, 1)[:2]
+    assert _bits_equal(res, small(c0, c1, 2))
+    assert _bits_equal(res, big(c0, c1, 2)[:2])
 
 
 def test_batch8x1024_sampled_heads():
