@@ -624,9 +624,11 @@ int lacache_first_layer_tokens(void* stream, const int32_t* token_ids, const int
   void* base = nullptr;
   RETURN_IF(get_workspace(static_cast<hipStream_t>(stream), lacache_first_layer_workspace_bytes(R, heads, H), &base));
   uint16_t* y = static_cast<uint16_t*>(base);
+  // the positions of the rows whose token id and position are in range, else -1
+  int32_t* dst = reinterpret_cast<int32_t*>(static_cast<char*>(base) + align256(static_cast<size_t>(R * H) * 2));
   hipStream_t st = static_cast<hipStream_t>(stream);
-  RETURN_IF(hip_status(launch_embed_rmsnorm(st, token_ids, rows, R, embed, vocab, norm_w, embed_cache, N, y, H)));
-  return hip_status(launch_linear_rope(st, y, w_qkv, rows, R, rope_cos, rope_sin, q, k, v, heads, N, H));
+  RETURN_IF(hip_status(launch_embed_rmsnorm(st, token_ids, rows, R, embed, vocab, norm_w, embed_cache, N, y, H, dst)));
+  return hip_status(launch_linear_rope(st, y, w_qkv, dst, R, rope_cos, rope_sin, q, k, v, heads, N, H));
 }
 
 int lacache_add_bf16(void* stream, uint16_t* x_inout, const uint16_t* y, int64_t n) {

@@ -38,20 +38,25 @@ typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 // lane), and normalizes and writes the passes t with t mod (1 << wpr_log2)
 // equal to its index, which shortens a short call (the first layer at 32 rows of
 // 4096: 26.4 us with one wavefront per row, 24.6 with four).
+// dst (nullable) [R]: the row's position, or -1 where its token id or position is
+// out of range (nothing else is written for it), for the projection's epilogue.
 template <int T>
 __global__ __launch_bounds__(256) void embed_rmsnorm_kernel(const int32_t* __restrict__ ids,
                                                             const int32_t* __restrict__ rows, int64_t R,
                                                             const uint16_t* __restrict__ embed, int64_t vocab,
                                                             const uint16_t* __restrict__ nw,
                                                             uint16_t* __restrict__ cache, int64_t N,
-                                                            uint16_t* __restrict__ y, int H, int wpr_log2) {
+                                                            uint16_t* __restrict__ y, int H, int wpr_log2,
+                                                            int32_t* __restrict__ dst) {
   const int lane = threadIdx.x & 63;
   const int wave = wave_uniform(threadIdx.x >> 6);
   const int part = wave & ((1 << wpr_log2) - 1);
   const int64_t r = (static_cast<int64_t>(blockIdx.x) * 4 + wave) >> wpr_log2;
   if (r >= R) return;  // uniform per wavefront
   const int64_t id = ids[r], pos = rows[r];
-  if (id < 0 || id >= vocab || pos < 0 || pos >= N) return;
+  const bool ok = id >= 0 && id < vocab && pos >= 0 && pos < N;
+  if (dst != nullptr && part == 0 && lane == 0) dst[r] = ok ? static_cast<int32_t>(pos) : -1;
+  if (!ok) return;
   const int nchunk = H >> 3;
   const uint4* xr = reinterpret_cast<const uint4*>(embed + id * H);
   const uint4* wr = reinterpret_cast<const uint4*>(nw);
@@ -97,7 +102,8 @@ __global__ __launch_bounds__(256) void embed_rmsnorm_kernel(const int32_t* __res
 // consecutive: a pair (i, i + 64) of a head meets in one wavefront, so the
 // tile takes P consecutive pairs of the 64 3 heads (pair p: head p / 64, i =
 // p mod 64) and weight rows i and i + 64 for each. Rows whose position is
-// outside [0, N) write nothing.
+// outside [0, N) write nothing (the whole call passes the positions that the
+// embedding kernel checked: the y of a row with a bad token id is never written).
 struct RopeArgs {
   const int32_t* rows;
   const float* cs;
@@ -541,14 +547,14 @@ __global__ __launch_bounds__(256) void rope_scatter_kernel(const uint16_t* __res
 
 hipError_t launch_embed_rmsnorm(hipStream_t st, const int32_t* ids, const int32_t* rows, int64_t R,
                                 const uint16_t* embed, int64_t vocab, const uint16_t* nw, uint16_t* cache, int64_t N,
-                                uint16_t* y, int64_t H) {
+                                uint16_t* y, int64_t H, int32_t* dst) {
   const int T = static_cast<int>((H + 511) / 512);
   // up to 1024 rows (4 wavefronts per SIMD): up to four wavefronts per row
   const int wl = R > 1024 ? 0 : (T >= 4 ? 2 : (T >= 2 ? 1 : 0));
   const dim3 grid(static_cast<unsigned>(((R << wl) + 3) / 4)), block(256);
   const int h = static_cast<int>(H);
 #define ER(T_) \
-  hipLaunchKernelGGL(embed_rmsnorm_kernel<T_>, grid, block, 0, st, ids, rows, R, embed, vocab, nw, cache, N, y, h, wl)
+  hipLaunchKernelGGL(embed_rmsnorm_kernel<T_>, grid, block, 0, st, ids, rows, R, embed, vocab, nw, cache, N, y, h, wl, dst)
   if (T <= 1) ER(1);
   else if (T <= 2) ER(2);
   else if (T <= 4) ER(4);

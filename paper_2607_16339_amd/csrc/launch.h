@@ -103,7 +103,7 @@ hipError_t launch_down_skinny(hipStream_t st, const uint8_t* hq, const float* hs
 // and rows outside [0, N) are skipped on the device.
 hipError_t launch_embed_rmsnorm(hipStream_t st, const int32_t* ids, const int32_t* rows, int64_t R,
                                 const uint16_t* embed, int64_t vocab, const uint16_t* nw, uint16_t* cache, int64_t N,
-                                uint16_t* y, int64_t H);
+                                uint16_t* y, int64_t H, int32_t* dst = nullptr);
 hipError_t launch_linear_bf16(hipStream_t st, const uint16_t* a, const uint16_t* w, uint16_t* out, float* out_tap,
                               int64_t M, int64_t N, int64_t K);
 // q, k, v rows of RoPE(y w_qkv^T) (rows [R], w_qkv [3 heads 128 x H]): the

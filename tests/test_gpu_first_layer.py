@@ -287,3 +287,28 @@ def test_fused_rope_epilogue_equals_the_stages(R, heads, H):
     for a, b in zip(fused, staged):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
     assert not torch.isnan(fused[1][:, rows[-1]].float()).any()
+
+
+@pytest.mark.parametrize("R,heads,H", [(9, 2, 256), (40, 32, 256), (300, 2, 128), (300, 32, 128), (1000, 32, 128)])
+def test_invalid_ids_write_nothing_in_the_fused_call(R, heads, H):
+    """An entry whose token id is outside the vocabulary writes no row of any
+    cache, on the streaming kernel (9, 40 rows) and on every tile shape (300
+    and 1000), whatever an earlier call left in the workspace."""
+    N, vocab = R + 3, 100
+    rng, embed, nw, wqkv, cos_t, sin_t = _setup(H, heads, N, vocab, seed=R + heads)
+    ids = rng.integers(0, vocab, R)
+    rows = rng.permutation(N)[:R]
+    _full_call(ids, rows, embed, nw, wqkv, cos_t, sin_t, _caches(heads, N, H))  # fills the workspace
+    bad = np.unique([1, R // 2, R - 1])
+    ids[bad] = [-1, vocab, 2 ** 31 - 1][:len(bad)]
+    _say("bad ids R=%d heads=%d H=%d" % (R, heads, H))
+    fused, staged = _caches(heads, N, H, fill=0x1234), _caches(heads, N, H, fill=0x1234)
+    _full_call(ids, rows, embed, nw, wqkv, cos_t, sin_t, fused)
+    good = np.setdiff1d(np.arange(R), bad)
+    _full_call(ids[good], rows[good], embed, nw, wqkv, cos_t, sin_t, staged)
+    torch.cuda.synchronize()
+    assert np.all(host_bf16(fused[0])[rows[bad]] == 0x1234)
+    for t in fused[1:]:
+        assert np.all(host_bf16(t)[:, rows[bad]] == 0x1234)
+    for a, b in zip(fused, staged):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
