@@ -131,12 +131,18 @@ __device__ __forceinline__ uint32_t f32_to_bf16(float f) {
 }
 
 // Two values -> bf16 in one v_cvt_pk_bf16_f32: the bits of f32_to_bf16 for
-// every fp32 value (checked over all of them); a NaN stays a NaN, with its own
-// sign and payload.
+// every fp32 value but NaNs, which keep their sign and payload.
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t cvt_pk_bf16(float lo, float hi) {
   const bf16x2 v = {static_cast<__bf16>(lo), static_cast<__bf16>(hi)};
   return __builtin_bit_cast(uint32_t, v);
+}
+
+// A word of cvt_pk_bf16 with 0x7FC0 in the place of every NaN.
+__device__ __forceinline__ uint32_t bf16x2_quiet(uint32_t w) {
+  if ((w & 0x7FFFu) > 0x7F80u) w = (w & 0xFFFF0000u) | 0x7FC0u;
+  if ((w & 0x7FFF0000u) > 0x7F800000u) w = (w & 0xFFFFu) | 0x7FC00000u;
+  return w;
 }
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {

@@ -90,8 +90,18 @@ __global__ __launch_bounds__(256) void embed_rmsnorm_kernel(const int32_t* __res
     if ((t & ((1 << wpr_log2) - 1)) != part || c >= nchunk) continue;
     float n[8];
     norm8(xv[t], wv[t], rs, n);
-    reinterpret_cast<uint4*>(y + r * H)[c] = make_uint4(cvt_pk_bf16(n[0], n[1]), cvt_pk_bf16(n[2], n[3]),
-                                                        cvt_pk_bf16(n[4], n[5]), cvt_pk_bf16(n[6], n[7]));
+    uint32_t o[4];
+    bool nan = false;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      nan |= __builtin_isunordered(n[2 * e], n[2 * e + 1]) != 0;
+      o[e] = cvt_pk_bf16(n[2 * e], n[2 * e + 1]);
+    }
+    if (__builtin_expect(nan, 0)) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = bf16x2_quiet(o[e]);
+    }
+    reinterpret_cast<uint4*>(y + r * H)[c] = make_uint4(o[0], o[1], o[2], o[3]);
   }
 }
 
@@ -117,6 +127,12 @@ struct RopeArgs {
 __device__ __forceinline__ uint16_t* rope_dst(const RopeArgs& ra, int head) {
   const int part = head / ra.heads;
   return (part == 0 ? ra.q : (part == 1 ? ra.k : ra.v)) + static_cast<int64_t>(head - part * ra.heads) * ra.N * 128;
+}
+
+// The four bf16 values that this lane stored at p, NaNs as 0x7FC0.
+__device__ __forceinline__ void quiet_stored(uint2* p) {
+  const uint2 v = *p;
+  *p = make_uint2(bf16x2_quiet(v.x), bf16x2_quiet(v.y));
 }
 
 // out [M x N] = a [M x K] W[N x K]^T, bf16 in and out, fp32 accumulation.
@@ -256,8 +272,11 @@ __global__ __launch_bounds__(kLinSplit * 64) void linear_bf16_kernel(const uint1
       uint32_t xy = cvt_pk_bf16(x, y);
       if (head < 2 * ra.heads) {
         const float c = ra.cs[pos * 64 + i], s = ra.sn[pos * 64 + i], xb = bf16lo(xy), yb = bf16hi(xy);
-        xy = cvt_pk_bf16(xb * c - yb * s, yb * c + xb * s);
+        x = xb * c - yb * s;
+        y = yb * c + xb * s;
+        xy = cvt_pk_bf16(x, y);
       }
+      if (__builtin_isunordered(x, y)) xy = bf16x2_quiet(xy);
       dst[0] = static_cast<uint16_t>(xy);
       dst[64] = static_cast<uint16_t>(xy >> 16);
     }
@@ -269,7 +288,7 @@ __global__ __launch_bounds__(kLinSplit * 64) void linear_bf16_kernel(const uint1
     float sum = red[row * NC + col];
 #pragma unroll
     for (int wv = 1; wv < kLinSplit; ++wv) sum += red[(wv * RA + row) * NC + col];
-    out[(m0 + row) * N + n0 + col] = static_cast<uint16_t>(cvt_pk_bf16(sum, 0.0f));
+    out[(m0 + row) * N + n0 + col] = static_cast<uint16_t>(sum == sum ? cvt_pk_bf16(sum, 0.0f) : 0x7FC0u);
     if (out_tap != nullptr) out_tap[(m0 + row) * N + n0 + col] = sum;
   }
 }
@@ -467,10 +486,17 @@ __global__ __launch_bounds__(kLtWaves * 64) void linear_bf16_tiled_kernel(const 
         const int64_t row = m0 + 16 * (MT * wm + i) + lr;
         const int64_t pos = row < M ? ra.rows[row] : -1;
         if (pos < 0 || pos >= ra.N) continue;
+        auto place = [&](int j, int& head, int& i0) {
+          const int ps = ct * (BN / 32) + wn * (NT / 2) + j;
+          head = ps >> 2;
+          i0 = (ps & 3) * 16 + 4 * q;
+          return rope_dst(ra, head) + pos * 128 + i0;
+        };
+        bool nan = false;
 #pragma unroll
         for (int j = 0; j < NT / 2; ++j) {
-          const int ps = ct * (BN / 32) + wn * (NT / 2) + j, head = ps >> 2, i0 = (ps & 3) * 16 + 4 * q;
-          uint16_t* dst = rope_dst(ra, head) + pos * 128 + i0;
+          int head, i0;
+          uint16_t* dst = place(j, head, i0);
           const v4f x = tot[i][j], y = tot[i][j + NT / 2];
           uint32_t lo[2] = {cvt_pk_bf16(x[0], x[1]), cvt_pk_bf16(x[2], x[3])};
           uint32_t hi[2] = {cvt_pk_bf16(y[0], y[1]), cvt_pk_bf16(y[2], y[3])};
@@ -480,12 +506,29 @@ __global__ __launch_bounds__(kLtWaves * 64) void linear_bf16_tiled_kernel(const 
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
               const float x0 = bf16lo(lo[e]), x1 = bf16hi(lo[e]), y0 = bf16lo(hi[e]), y1 = bf16hi(hi[e]);
-              lo[e] = cvt_pk_bf16(x0 * c[2 * e] - y0 * s[2 * e], x1 * c[2 * e + 1] - y1 * s[2 * e + 1]);
-              hi[e] = cvt_pk_bf16(y0 * c[2 * e] + x0 * s[2 * e], y1 * c[2 * e + 1] + x1 * s[2 * e + 1]);
+              const float a0 = x0 * c[2 * e] - y0 * s[2 * e], a1 = x1 * c[2 * e + 1] - y1 * s[2 * e + 1];
+              const float b0 = y0 * c[2 * e] + x0 * s[2 * e], b1 = y1 * c[2 * e + 1] + x1 * s[2 * e + 1];
+              lo[e] = cvt_pk_bf16(a0, a1);
+              hi[e] = cvt_pk_bf16(b0, b1);
+              nan |= __builtin_isunordered(a0, a1) || __builtin_isunordered(b0, b1);
             }
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; e += 2) nan |= __builtin_isunordered(x[e], x[e + 1]) || __builtin_isunordered(y[e], y[e + 1]);
           }
           *reinterpret_cast<uint2*>(dst) = make_uint2(lo[0], lo[1]);
           *reinterpret_cast<uint2*>(dst + 64) = make_uint2(hi[0], hi[1]);
+        }
+        if (__builtin_expect(nan, 0)) {
+          // a NaN is stored as 0x7FC0: this lane's values once more (rare, so not
+          // worth the instructions for every value above)
+#pragma unroll 1
+          for (int j = 0; j < NT / 2; ++j) {
+            int head, i0;
+            uint2* dst = reinterpret_cast<uint2*>(place(j, head, i0));
+            quiet_stored(dst);
+            quiet_stored(dst + 16);
+          }
         }
       }
       continue;  // the next item
@@ -496,10 +539,17 @@ __global__ __launch_bounds__(kLtWaves * 64) void linear_bf16_tiled_kernel(const 
       const int64_t row = m0 + 16 * (MT * wm + i) + lr;
       if (row >= M) continue;
       uint16_t* o = out + row * N + col0;
+      bool nan = false;
 #pragma unroll
-      for (int j = 0; j < NT; ++j)
+      for (int j = 0; j < NT; ++j) {
+        nan |= __builtin_isunordered(tot[i][j][0], tot[i][j][1]) || __builtin_isunordered(tot[i][j][2], tot[i][j][3]);
         *reinterpret_cast<uint2*>(o + 16 * j) =
             make_uint2(cvt_pk_bf16(tot[i][j][0], tot[i][j][1]), cvt_pk_bf16(tot[i][j][2], tot[i][j][3]));
+      }
+      if (__builtin_expect(nan, 0)) {  // (as in the RoPE epilogue)
+#pragma unroll 1
+        for (int j = 0; j < NT; ++j) quiet_stored(reinterpret_cast<uint2*>(o + 16 * j));
+      }
     }
     if (out_tap != nullptr) {
 #pragma unroll

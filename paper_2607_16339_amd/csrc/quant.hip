@@ -85,6 +85,26 @@ hipError_t launch_pack_weights(hipStream_t st, const uint8_t* w, uint8_t* wt, in
 }
 
 // ---------------------------------------------------------------------------
+// 8 residual values, RNE_bf16(float(x) + float(y)). Sums that are NaN keep their
+// bits in the one-instruction conversion, and set nan; quiet_bf16x8 then makes
+// them 0x7FC0 (a comparison per two values in the usual case).
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ uint4 add_bf16x8(uint4 x, uint4 y, bool& nan) {
+  const uint32_t a[4] = {x.x, x.y, x.z, x.w}, b[4] = {y.x, y.y, y.z, y.w};
+  uint32_t s[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float lo = bf16lo(a[e]) + bf16lo(b[e]), hi = bf16hi(a[e]) + bf16hi(b[e]);
+    nan |= __builtin_isunordered(lo, hi) != 0;
+    s[e] = cvt_pk_bf16(lo, hi);
+  }
+  return make_uint4(s[0], s[1], s[2], s[3]);
+}
+__device__ __forceinline__ uint4 quiet_bf16x8(uint4 v) {
+  return make_uint4(bf16x2_quiet(v.x), bf16x2_quiet(v.y), bf16x2_quiet(v.z), bf16x2_quiet(v.w));
+}
+
+// ---------------------------------------------------------------------------
 // Fused RMSNorm + 1x128 quantization. A row belongs to 1 << wpr_log2
 // wavefronts; lane l of each holds chunks c = 64 t + l (8 bf16 each) for
 // t < T, so a 128-wide group is the 16 lanes 16g'..16g'+15 of one pass. The
@@ -132,12 +152,12 @@ __global__ __launch_bounds__(256, T <= 8 && !kAdd ? 4 : 1) void rmsnorm_quant_ke
     if constexpr (kAdd) yv[t] = reinterpret_cast<const uint4*>(y + row * H)[cc];
   }
   if constexpr (kAdd) {  // the residual add, in registers (written back below)
+    bool nan = false;
 #pragma unroll
-    for (int t = 0; t < T; ++t) {
-      uint32_t* a = reinterpret_cast<uint32_t*>(&xv[t]);
-      const uint32_t* b = reinterpret_cast<const uint32_t*>(&yv[t]);
+    for (int t = 0; t < T; ++t) xv[t] = add_bf16x8(xv[t], yv[t], nan);
+    if (__builtin_expect(nan, 0)) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) a[e] = cvt_pk_bf16(bf16lo(a[e]) + bf16lo(b[e]), bf16hi(a[e]) + bf16hi(b[e]));
+      for (int t = 0; t < T; ++t) xv[t] = quiet_bf16x8(xv[t]);
     }
   }
 #pragma unroll
@@ -279,17 +299,13 @@ __global__ __launch_bounds__(256) void add_bf16_kernel(uint16_t* __restrict__ x,
                                                        int64_t n) {
   const int64_t i8 = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) * 8;
   if (i8 + 8 <= n) {
-    uint4 a = *reinterpret_cast<const uint4*>(x + i8);
-    const uint4 b = *reinterpret_cast<const uint4*>(y + i8);
-    uint32_t* pa = reinterpret_cast<uint32_t*>(&a);
-    const uint32_t* pb = reinterpret_cast<const uint32_t*>(&b);
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      pa[e] = cvt_pk_bf16(bf16lo(pa[e]) + bf16lo(pb[e]), bf16hi(pa[e]) + bf16hi(pb[e]));
+    bool nan = false;
+    uint4 a = add_bf16x8(*reinterpret_cast<const uint4*>(x + i8), *reinterpret_cast<const uint4*>(y + i8), nan);
+    if (__builtin_expect(nan, 0)) a = quiet_bf16x8(a);
     *reinterpret_cast<uint4*>(x + i8) = a;
   } else {
     for (int64_t i = i8; i < n; ++i)
-      x[i] = static_cast<uint16_t>(cvt_pk_bf16(bf16lo(x[i]) + bf16lo(y[i]), 0.0f));
+      x[i] = static_cast<uint16_t>(f32_to_bf16(bf16lo(x[i]) + bf16lo(y[i])));
   }
 }
 

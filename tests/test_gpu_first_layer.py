@@ -312,3 +312,46 @@ def test_invalid_ids_write_nothing_in_the_fused_call(R, heads, H):
         assert np.all(host_bf16(t)[:, rows[bad]] == 0x1234)
     for a, b in zip(fused, staged):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+@pytest.mark.parametrize("R,heads,H", [(5, 2, 256), (300, 2, 128), (300, 32, 128), (1000, 32, 128)])
+def test_nans_are_stored_as_one_pattern(R, heads, H):
+    """A NaN of the norm, the projection or RoPE is stored as the quiet NaN
+    0x7FC0, whatever the sign and payload of the embedding's, the weights' or the
+    tables', on the streaming kernel and on every tile shape, staged and fused;
+    rows and heads that meet none hold none."""
+    N, vocab = R, 100
+    rng, embed, nw, wqkv, cos_t, sin_t = _setup(H, heads, N, vocab, seed=R + heads)
+    for i, bits in enumerate((0x7F81, 0xFF81, 0xFFC5, 0x7FFF, 0xFF80)):  # NaNs; -inf: its row's norm holds 0 and a NaN
+        embed[i, 7 * i] = bits
+    ids = rng.integers(5, vocab, R)
+    nan_rows = np.arange(0, 5) * (R // 5)
+    ids[nan_rows] = np.arange(5)
+    rows = np.arange(R)
+    wqkv[heads * D + 3], wqkv[3 * heads * D - 5, 9], wqkv[7, 0] = 0xFFC5, 0x7F81, 0xFF80  # rows of k, v and q
+    tab = rng.permutation(R)[:3]
+    cos_t.view(np.uint32)[tab[0], :] = 0xFFC12345
+    sin_t.view(np.uint32)[tab[1], ::2] = 0x7F800001
+    cos_t[tab[2]] = -np.inf
+    _say("NaNs R=%d heads=%d H=%d" % (R, heads, H))
+    fused = _caches(heads, N, H, fill=0x1234)
+    _full_call(ids, rows, embed, nw, wqkv, cos_t, sin_t, fused)
+    cache, _, _, _ = _caches(heads, N, H)
+    y = torch.empty((R, H), dtype=torch.bfloat16, device=DEV)
+    qkv = torch.empty((R, 3 * heads * D), dtype=torch.bfloat16, device=DEV)
+    lc.lacache_embed_rmsnorm(_i32(ids), _i32(rows), dev_bf16(embed), dev_bf16(nw), cache, y)
+    lc.lacache_linear_bf16(y, dev_bf16(wqkv), qkv)
+    torch.cuda.synchronize()
+    assert np.array_equal(host_bf16(fused[0])[nan_rows], embed[:5])  # a copy, payloads kept
+    yy, pp = host_bf16(y), host_bf16(qkv)
+    nan = lambda b: (b & 0x7FFF) > 0x7F80  # noqa: E731
+    for a in [yy, pp] + [host_bf16(t) for t in fused[1:]]:
+        assert np.all(a[nan(a)] == 0x7FC0)
+    assert np.all(nan(yy[nan_rows[:4]])) and nan(yy[nan_rows[4]]).sum() == 1
+    assert np.all(nan(pp[nan_rows]))
+    others = np.setdiff1d(rows, np.concatenate([nan_rows, tab]))
+    cols = [np.setdiff1d(np.arange(D), c) for c in ([7, 71], [3, 67], [D - 5])]
+    for t, c in zip(fused[1:], cols):
+        b = host_bf16(t)
+        assert np.all(nan(b[:, nan_rows]))
+        assert not nan(b[:, others][:, :, c]).any()

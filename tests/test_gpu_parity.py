@@ -34,6 +34,7 @@ from gpu_util import (DEV, Layer, check_down_model, check_down_same_operands, ch
                       check_gateup_model, check_norm_exact, check_requant_exact, dev_bf16, host, host_bf16,
                       mfma_dot_bound, run_stages)
 from oracle import csweep
+from oracle.bf16 import bf16_to_f32, rne_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -871,6 +872,52 @@ def test_residual_add_bit_exact():
     lc.lacache_add_bf16(x, dev_bf16(bb))
     torch.cuda.synchronize()
     assert np.array_equal(host_bf16(x), O.residual_add(ab, bb))
+
+
+# bf16 NaNs of both signs, signalling and quiet, with payloads; infinities
+SPECIAL = [0x7F81, 0xFF81, 0x7FC0, 0xFFC0, 0x7FFF, 0xFFD5, 0x7F80, 0xFF80]
+
+
+def _add_with_nans(xb, yb):
+    with np.errstate(invalid="ignore"):
+        s = (bf16_to_f32(xb) + bf16_to_f32(yb)).astype(np.float32)
+    nan = np.isnan(s)
+    return np.where(nan, np.uint16(0x7FC0), rne_bf16(np.where(nan, np.float32(0), s)))
+
+
+@pytest.mark.parametrize("H", [128, 1024, 4096])
+def test_residual_add_of_nans_and_infinities(H):
+    """A NaN sum is stored as the quiet NaN 0x7FC0, whatever its operands' sign
+    and payload (inf - inf included), in the residual add and in the AddNorm;
+    rows of any bits, subnormal values among them, round to nearest even."""
+    _say("residual add of NaNs, H=%d" % H)
+    rng = np.random.default_rng(H)
+    M = 40
+    xb = synth.to_bf16_bits(rng.standard_normal((M, H)).astype(np.float32))
+    yb = synth.to_bf16_bits(rng.standard_normal((M, H)).astype(np.float32))
+    for i, a in enumerate(SPECIAL):
+        xb[i, rng.integers(0, H, 4)] = a
+        yb[8 + i, rng.integers(0, H, 4)] = a
+        for j, b in enumerate(SPECIAL):
+            xb[16 + i, 5 + 9 * j], yb[16 + i, 5 + 9 * j] = a, b
+    xb[24:32] = rng.integers(0, 1 << 16, (8, H))  # any bits, subnormal ones and sums among them
+    yb[24:28] = rng.integers(0, 1 << 16, (4, H))
+    yb[28:32] = xb[28:32] ^ rng.integers(0, 1 << 10, (4, H)).astype(np.uint16)
+    xb[32], yb[32] = rng.integers(0, 0x200, H), rng.integers(0, 0x200, H) | 0x8000
+    want = _add_with_nans(xb, yb)
+    x = dev_bf16(xb)
+    lc.lacache_add_bf16(x, dev_bf16(yb))
+    r = dev_bf16(xb)
+    xq = torch.full((M, H), 0xFF, dtype=torch.uint8, device=DEV)
+    xs = torch.full((H // 128, M), float("nan"), dtype=torch.float32, device=DEV)
+    lc.lacache_add_rmsnorm_quant(r, dev_bf16(yb), dev_bf16(np.full(H, 0x3F80, dtype=np.uint16)), xq, xs)
+    odd = dev_bf16(xb[16:24, :59].ravel()[:-1])  # 8 n - 1 values: the last ones one by one
+    odd[-1] = float("nan")
+    lc.lacache_add_bf16(odd, dev_bf16(yb[16:24, :59].ravel()[:-1]))
+    torch.cuda.synchronize()
+    assert np.array_equal(host_bf16(x), want)
+    assert np.array_equal(host_bf16(r), want)
+    assert np.array_equal(host_bf16(odd)[:-1], want[16:24, :59].ravel()[:-2]) and host_bf16(odd)[-1] == 0x7FC0
 
 
 def test_zero_rows_is_a_no_op(big_layer):
