@@ -434,6 +434,14 @@ size_t lacache_first_layer_workspace_bytes(int64_t R, int64_t heads, int64_t H);
  */
 int lacache_set_path_policy(int policy);
 
+/* Test hook: what the tiled kernels take for a call of these sizes on the
+ * current device (256 compute units where the runtime cannot tell), with
+ * per-channel weight scales (col_scales != 0: the coarse granularities) or
+ * without: plan[0] the gate/up row-tile height, plan[1], plan[2] the down GEMM's
+ * tile rows and columns, plan[3] its K splits, plan[4] 1 if its weights go
+ * straight to registers. M > 0. Launches nothing. */
+int lacache_tiled_plan(int64_t M, int64_t H, int64_t I, int col_scales, int* plan);
+
 /* Human-readable name of a status code (static string). */
 const char* lacache_status_string(int status);
 

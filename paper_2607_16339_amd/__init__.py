@@ -6,6 +6,8 @@ pass raw pointers and the current HIP stream, and raise ``LacacheError`` on a
 non-OK status. Every step of the FFN runs in the library's HIP kernels.
 """
 
+import ctypes
+
 import numpy as np
 import torch
 
@@ -310,6 +312,14 @@ def lacache_set_path_policy(policy):
     if r < 0:
         raise LacacheError(r, "lacache_set_path_policy")
     return r
+
+
+def lacache_tiled_plan(M, H, I, col_scales=False):
+    """(gate/up tile rows, down tile rows, down tile columns, down K splits, down weights in
+    registers) of the tiled kernels for a call of these sizes on the current device."""
+    plan = (ctypes.c_int * 5)()
+    check(lib().lacache_tiled_plan(M, H, I, int(col_scales), plan), "lacache_tiled_plan")
+    return plan[0], plan[1], plan[2], plan[3], bool(plan[4])
 
 
 def lacache_status_string(status):

@@ -506,6 +506,17 @@ int lacache_down_proj_g(void* stream, const uint8_t* hq, const float* hs, const 
                                       scratch, wd_row_s));
 }
 
+int lacache_tiled_plan(int64_t M, int64_t H, int64_t I, int col_scales, int* plan) {
+  RETURN_IF(check_m(M));
+  RETURN_IF(check_dim(H, kMaxH));
+  RETURN_IF(check_dim(I, kMaxI));
+  if (M == 0 || plan == nullptr) return LACACHE_ERR_INVALID_ARG;
+  int p[5];
+  tiled_plan(M, H, I, col_scales != 0, p);
+  std::memcpy(plan, p, sizeof(p));
+  return LACACHE_OK;
+}
+
 size_t lacache_ffn_g_workspace_bytes(int64_t M, int64_t H, int64_t I) {
   if (check_m(M) != LACACHE_OK || check_dim(H, kMaxH) != LACACHE_OK || check_dim(I, kMaxI) != LACACHE_OK) return 0;
   const size_t m = static_cast<size_t>(M);

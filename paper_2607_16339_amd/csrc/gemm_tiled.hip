@@ -532,9 +532,9 @@ size_t tiled_down_ws_bytes(int64_t M, int64_t H, int64_t I) {
   return ks > 1 ? static_cast<size_t>(ks) * static_cast<size_t>(M) * static_cast<size_t>(H) * 4 : 0;
 }
 
-hipError_t launch_gateup_tiled(hipStream_t st, const uint8_t* xq, const float* xs, const uint8_t* wq,
-                               const float* ws, uint8_t* hq, float* hs, float* h_tap, int64_t M, int64_t H,
-                               int64_t I, const float* col_s) {
+namespace {
+
+int gateup_height(int64_t M, int64_t H, int64_t I) {
   // Row-tile height: the least loop time. Every height gives the same bytes (an
   // element's K-groups are added in the same order). K-group times fitted to
   // sweeps at H = 512..8192, I = 6144..24576 and M = 65..2048; at H = 4096, I =
@@ -549,10 +549,18 @@ hipError_t launch_gateup_tiled(hipStream_t st, const uint8_t* xq, const float* x
     const double us = loops_us(((M + kHeights[t] - 1) / kHeights[t]) * (I / 128), H / 128, kGroup[t][0], kGroup[t][1]);
     if (t == 0 || us < best) pick = t, best = us;
   }
+  return kHeights[pick];
+}
+
+}  // namespace
+
+hipError_t launch_gateup_tiled(hipStream_t st, const uint8_t* xq, const float* xs, const uint8_t* wq,
+                               const float* ws, uint8_t* hq, float* hs, float* h_tap, int64_t M, int64_t H,
+                               int64_t I, const float* col_s) {
 #define GU(BM_)                                                                                                    \
   return launch_tiled<true, BM_, 256>(st, xq, xs, wq, ws, hq, hs, h_tap, nullptr, nullptr, nullptr, M, H, 2 * I, I, 1, \
                                       col_s)
-  switch (kHeights[pick]) {
+  switch (gateup_height(M, H, I)) {
     case 64: GU(64);
     case 96: GU(96);
     case 128: GU(128);
@@ -562,50 +570,83 @@ hipError_t launch_gateup_tiled(hipStream_t st, const uint8_t* xq, const float* x
 #undef GU
 }
 
+namespace {
+
+struct DownPlan {
+  int shape;  // of kDownShapes
+  int ks;     // K splits
+  bool regs;  // 64 x 128 tiles by the kernel with the weights in registers
+};
+struct DownShape {
+  int bm, bn;
+  double start, c0, c1;
+};
+constexpr DownShape kDownShapes[4] = {
+    {256, 256, 9.5, 0.85, 0.0}, {128, 256, 6.3, 0.55, 0.02}, {128, 128, 5.8, 0.32, 0.08}, {64, 128, 6.3, 0.26, 0.0}};
+constexpr DownShape kDownRegs = {64, 128, 3.8, 0.24, 0.04};
+
+// Tile shape and K splits (up to the partials the workspace holds): the least of
+// start-up + loops + the partials' reduction (a launch, and writing and reading
+// them). 64-row tiles take their weights into registers wherever that kernel fits
+// one round (at M = 65..1024 it was the faster one at every split, by 0.4 to 4 us
+// of the whole FFN). The constants are fitted to the whole FFN call at 188 sizes, M =
+// 65..8192, H = 128..16384, I = 1024..16384, all shapes and splits in turn in one
+// process; the chosen one is on average 0.13 % slower than the best, 4.8 % at most.
+// 128 x 256 tiles over the workspace's splits stay unless another choice is more
+// than 1 us less, about the fit's error: at H = 4096, I = 12288 the whole FFN
+// takes, in us, with them, with the best other shape and split, and as chosen:
+// M = 128 65.2, 59.6, 60.4; 256 73.6, 71.0, 71.0; 400 96.2, 96.5, 96.2; 512 98.8,
+// 100.8, 98.8; at H = 3072, I = 8192, M = 400 59.3, 55.6, 55.6 (64 x 128 tiles
+// without a split; 60.9 where the rule took them with three).
+DownPlan down_plan(int64_t M, int64_t H, int64_t I, bool col_scales) {
+  const int ks_max = down_splits(M, H, I);
+  constexpr double kMargin = 1.0;
+  DownPlan pick{1, ks_max, false};
+  double best = 0.0;
+  auto us = [&](int t, int k, bool regs) {
+    const DownShape& s = regs ? kDownRegs : kDownShapes[t];
+    const int64_t tiles = ((M + s.bm - 1) / s.bm) * ((H + s.bn - 1) / s.bn);
+    return s.start + loops_us(tiles * k, (I / 128 + k - 1) / k, s.c0, s.c1) +
+           (k > 1 ? 0.8 + (4.0 * k + 2.0) * static_cast<double>(M * H) / 3.5e6 : 0.0);
+  };
+  best = us(1, ks_max, false) - kMargin;
+  for (int t = 0; t < 4; ++t)
+    for (int k = 1; k <= (t == 0 ? 1 : ks_max); ++k) {
+      if (t == 1 && k == ks_max) continue;
+      const bool regs = t == 3 && !col_scales && down_rows64_ok(M, H, I, k);
+      const double e = us(t, k, regs);
+      if (e < best) pick = {t, k, regs}, best = e;
+    }
+  return pick;
+}
+
+}  // namespace
+
+void tiled_plan(int64_t M, int64_t H, int64_t I, bool col_scales, int (&plan)[5]) {
+  const DownPlan d = down_plan(M, H, I, col_scales);
+  plan[0] = gateup_height(M, H, I);
+  plan[1] = kDownShapes[d.shape].bm;
+  plan[2] = kDownShapes[d.shape].bn;
+  plan[3] = d.ks;
+  plan[4] = d.regs ? 1 : 0;
+}
+
 hipError_t launch_down_tiled(hipStream_t st, const uint8_t* hq, const float* hs, const uint8_t* wq, const float* ws,
                              uint16_t* out, float* out_tap, int64_t M, int64_t H, int64_t I, void* ws_buf,
                              const float* col_s) {
-  // Tile shape and K splits (up to the partials the workspace holds): the
-  // least of start-up + loops + the partials' reduction (a launch, and writing
-  // and reading them). Fitted to sweeps of all shapes and splits at H = 512..4096, I =
-  // 3072..12288, M = 65..4096; at H = 4096, I = 12288 the chosen one and 128 x
-  // 256 tiles alone take: M = 128 18.4 (64 x 128, 4 splits) and 25.2 us, M = 256
-  // 25.1 (128 x 128, 4) and 29.7, M = 512 37.3 (128 x 128, 2) and 39.6; at H =
-  // 1024, I = 3072, M = 512 12.5 (64 x 128, 1) and 24.1.
-  struct Shape {
-    int bm, bn;
-    double start, c0, c1;
-  };
-  constexpr Shape kShapes[4] = {
-      {256, 256, 9.0, 1.17, 0.53}, {128, 256, 6.3, 0.68, 0.37}, {128, 128, 5.7, 0.40, 0.15}, {64, 128, 5.8, 0.28, 0.06}};
-  const int ks_max = down_splits(M, H, I);
-  int pick = 0, ks = 1;
-  double best = 0.0;
-  for (int t = 0; t < 4; ++t) {
-    const Shape& s = kShapes[t];
-    const int64_t tiles = ((M + s.bm - 1) / s.bm) * ((H + s.bn - 1) / s.bn);
-    for (int k = 1; k <= (s.bm == 256 ? 1 : ks_max); ++k) {
-      // 64-row tiles with the weights in registers, up to the 4 row tiles that
-      // share one XCD's copy of them, are bound by each CU's own copies, however
-      // many CUs work (whole FFN at H = 4096, I = 12288, 128 x 128 tiles x 4 splits
-      // and these x 2: M = 192 71.7 and 73.1 us, 200 73.6 and 70.3, 256 73.8 and 72.7)
-      const bool regs = s.bm == 64 && col_s == nullptr && M <= 64 * kTileGroupRows && down_rows64_ok(M, H, I, k);
-      const double us = s.start + loops_us(tiles * k, (I / 128 + k - 1) / k, regs ? 0.33 : s.c0, regs ? -0.04 : s.c1) +
-                        (k > 1 ? 2.5 + (4.0 * k + 2.0) * static_cast<double>(M * H) / 7e6 : 0.0);
-      if ((t == 0 && k == 1) || us < best) pick = t, ks = k, best = us;
-    }
-  }
+  const DownPlan plan = down_plan(M, H, I, col_s != nullptr);
+  const int ks = plan.ks;
   float* part = static_cast<float*>(ws_buf);
   hipError_t e = hipSuccess;
 #define DN(BM_, BN_)                                                                                              \
   e = launch_tiled<false, BM_, BN_>(st, hq, hs, wq, ws, nullptr, nullptr, nullptr, out, out_tap, part, M, I, H, I, ks, \
                                     col_s)
-  switch (pick) {
+  switch (plan.shape) {
     case 0: DN(256, 256); break;
     case 1: DN(128, 256); break;
     case 2: DN(128, 128); break;
     default:
-      if (col_s == nullptr && down_rows64_ok(M, H, I, ks))
+      if (plan.regs)
         e = launch_down_rows64(st, hq, hs, wq, ws, out, out_tap, part, M, H, I, ks);
       else
         DN(64, 128);

@@ -80,6 +80,10 @@ hipError_t launch_down_tiled(hipStream_t st, const uint8_t* hq, const float* hs,
                              uint16_t* out, float* out_tap, int64_t M, int64_t H, int64_t I, void* ws_buf,
                              const float* col_s = nullptr);
 
+// What the two calls above take: {gate/up tile rows, down tile rows, down tile
+// columns, down K splits, 1 for the down kernel below}.
+void tiled_plan(int64_t M, int64_t H, int64_t I, bool col_scales, int (&plan)[5]);
+
 // Down GEMM on 64 x 128 tiles with the weights in registers: bit for bit the
 // tiled kernel's 64 x 128 tiles over ks K splits, for what down_rows64_ok accepts.
 bool down_rows64_ok(int64_t M, int64_t H, int64_t I, int ks);

@@ -496,12 +496,13 @@ def test_skinny_gateup_of_one_and_two_k_pieces():
     assert torch.equal(taps[0].view(torch.int32), taps[1][:48].view(torch.int32))
 
 
-@pytest.mark.parametrize("M,H,I", [(65, 128, 128), (100, 384, 768), (128, 256, 16384), (129, 512, 1536),
-                                   (200, 1024, 4224), (1000, 512, 1920)])
-def test_down_rows_of_64(M, H, I):
+@pytest.mark.parametrize("M,H,I,ks", [(65, 128, 128, 1), (100, 384, 768, 1), (128, 256, 16384, 8),
+                                      (129, 512, 1536, 1), (200, 1024, 4224, 2), (1000, 512, 1920, 1)])
+def test_down_rows_of_64(M, H, I, ks):
     """The down GEMM with its weights in registers: one K-group, K-group counts
     that leave 1, 2, 3 and all of the last chunk of 4, 8 K splits and 2 of unequal
     length, last row tiles of 1, 8, 36, 40 and 64 rows, up to 16 row tiles."""
+    _plan_is(M, H, I, (64, 128, ks, True))
     _say("down rows64 M=%d H=%d I=%d" % (M, H, I))
     lc.lacache_set_path_policy(2)
     w = synth.Workload(93, "rows64", M, H, I, act="outlier", outlier_ratio=0.02)
@@ -512,6 +513,71 @@ def test_down_rows_of_64(M, H, I):
     check_requant_exact(host(t["h_tap"]), host(t["hq"]), host(t["hs"]))
     check_down_same_operands(host(t["hq"]), host(t["hs"]), wd_q, wd_s, host(t["out_tap"]), host_bf16(t["out"]))
     check_down_model(host(t["hq"]), host(t["hs"]), wd_q, wd_s, host(t["out_tap"]))
+
+
+def _plan_is(M, H, I, down=None, gateup=None, col_scales=False):
+    """The tiled kernels take what the test is about: the down GEMM's (tile rows,
+    columns, K splits, weights in registers) and the gate/up tile height. (The
+    rule counts compute units; other devices than 256 run the sizes as they are.)"""
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        got = lc.lacache_tiled_plan(M, H, I, col_scales)
+        assert (down is None or got[1:] == down) and gateup in (None, got[0]), got
+
+
+def _random_down(M, H, I, seed):
+    """Operands of a down GEMM: finite codes, scales within a few binades."""
+    rng = np.random.default_rng(seed)
+    codes = lambda n, k: (rng.integers(0, 0x78, (n, k)) | (rng.integers(0, 2, (n, k)) << 7)).astype(np.uint8)  # noqa: E731
+    hq, wd = codes(M, I), codes(H, I)
+    hs = np.exp2(rng.uniform(-6, -2, (I // 128, M))).astype(np.float32)
+    ws = np.exp2(rng.uniform(-9, -7, (H // 128, I // 128))).astype(np.float32)
+    dev = [torch.from_numpy(a).to(DEV) for a in (hq, hs, lc.weight_codes_tiled(wd), ws)]
+    return (hq, hs, wd, ws), dev
+
+
+@pytest.mark.parametrize("M,H,I,down", [
+    (500, 4224, 128, (128, 256, 1, False)), (300, 4224, 12288, (128, 256, 5, False)),
+    (333, 3072, 12288, (128, 256, 6, False)), (2000, 4224, 2048, (256, 256, 1, False)),
+    (257, 8192, 384, (128, 128, 1, False)), (333, 3072, 8192, (128, 128, 3, False)),
+    (200, 3072, 12288, (128, 128, 5, False)), (65, 3072, 12288, (64, 128, 5, True))])
+def test_down_tile_shapes(M, H, I, down):
+    """Every down tile shape with and without K splits, ragged last row tiles,
+    partial column tiles of the 256-wide shapes (H = 4224: 128 valid columns, the
+    second block scale falling back to the first), a single K-group (I = 128)."""
+    _say("down M=%d H=%d I=%d %s" % (M, H, I, down))
+    _plan_is(M, H, I, down)
+    lc.lacache_set_path_policy(2)
+    (hq, hs, wd, ws), dev = _random_down(M, H, I, M + H + I)
+    out = torch.empty((M, H), dtype=torch.bfloat16, device=DEV)
+    tap = torch.full((M, H), float("nan"), dtype=torch.float32, device=DEV)
+    lc.lacache_down_proj(*dev, out, tap)
+    torch.cuda.synchronize()
+    assert torch.isfinite(tap).all().item()
+    rows = np.unique([0, down[0] - 1, down[0] % M, M // 2, M - 1])
+    check_down_same_operands(hq[rows], np.ascontiguousarray(hs[:, rows]), wd, ws, host(tap)[rows], host_bf16(out)[rows])
+    check_down_model(hq[rows], np.ascontiguousarray(hs[:, rows]), wd, ws, host(tap)[rows])
+
+
+@pytest.mark.parametrize("M,H,I,ks", [(129, 512, 1536, 1), (1000, 512, 1920, 1), (200, 1024, 4224, 2),
+                                      (190, 3072, 8192, 3), (128, 256, 16384, 8)])
+def test_down_weights_in_registers_give_the_tiled_kernels_bits(M, H, I, ks):
+    """The down GEMM with its weights in registers against the tiled kernel's 64 x
+    128 tiles over the same K splits (which calls with per-channel scales take;
+    the scales are ones): the same bits."""
+    _say("down registers against LDS M=%d H=%d I=%d" % (M, H, I))
+    _plan_is(M, H, I, (64, 128, ks, True))
+    _plan_is(M, H, I, (64, 128, ks, False), col_scales=True)
+    lc.lacache_set_path_policy(2)
+    _, dev = _random_down(M, H, I, M + H + I)
+    res = []
+    for f, extra in ((lc.lacache_down_proj, ()), (lc.lacache_down_proj_g, (torch.ones((H,), device=DEV),))):
+        out = torch.empty((M, H), dtype=torch.bfloat16, device=DEV)
+        tap = torch.full((M, H), float("nan"), dtype=torch.float32, device=DEV)
+        f(*dev, *extra, out, tap)
+        res.append((out, tap))
+    torch.cuda.synchronize()
+    assert torch.equal(res[0][1].view(torch.int32), res[1][1].view(torch.int32))
+    assert torch.equal(res[0][0].view(torch.int16), res[1][0].view(torch.int16))
 
 
 def _full_size_case(big_layer, w, step, rows_pick, policy):
@@ -569,22 +635,25 @@ def test_bm256_partial_row_tile_sampled(big_layer):
     w = synth.Workload(93, "bm256_partial", M, 4096, 12288, act="outlier", outlier_ratio=0.01)
     rows = lambda m: np.unique(np.concatenate([[0, 255, 256, 2815, 2816, m - 2, m - 1],
                                                np.random.default_rng(M).choice(np.arange(1, 2815), 4, replace=False)]))
+    _plan_is(M, 4096, 12288, (256, 256, 1, False), 256)
     g, e, d = _full_size_case(big_layer, w, 0, rows, 0)
     _say("bm256 partial M=%d: gate/up %s; down error %.2e, %.3f of the model tolerance" % (M, g, e, d))
 
 
-@pytest.mark.parametrize("M,ks", [(200, 6), (320, 5), (576, 3), (700, 2), (1024, 2)])
-def test_split_k_down_sampled(big_layer, M, ks):
-    """The tiled down GEMM with its K range split over KS workgroups per
-    output tile (as many as fit one round of one workgroup per CU on 256 CUs:
-    KS = 6 at 200 rows, 5 at 320, 3 at 576, 2 at 700 and 1024 for H = 4096,
-    I = 12288), oracle-checked on sampled rows, the first and last included."""
+@pytest.mark.parametrize("M,ks,down", [(200, 6, (64, 128, 2, True)), (320, 5, (128, 256, 5, False)),
+                                       (400, 4, (128, 256, 4, False)), (576, 3, (128, 256, 3, False)),
+                                       (700, 2, (128, 256, 2, False)), (1024, 2, (128, 128, 1, False))])
+def test_split_k_down_sampled(big_layer, M, ks, down):
+    """The tiled down GEMM at H = 4096, I = 12288: the K splits that its workspace
+    has room for (ks) and the tile shape and splits that it takes, oracle-checked
+    on sampled rows, the first and last included."""
     _say("split-K M=%d KS=%d" % (M, ks))
     if torch.cuda.get_device_properties(0).multi_processor_count == 256:
         # the workspace: the KS fp32 partials [KS][M][H], then xq [M][H] and
         # hq [M][3H] (I = 3H), i.e. (KS + 1) M H 4 bytes, plus the scales
         ws = lc.lacache_ffn_workspace_bytes(M, 4096, 12288)
         assert (ks + 1) * M * 4096 * 4 <= ws < (ks + 2) * M * 4096 * 4
+    _plan_is(M, 4096, 12288, down)
     w = synth.Workload(94, "splitk", M, 4096, 12288, act="outlier", outlier_ratio=0.01)
     rows = lambda m: np.concatenate([[0, m - 1], np.sort(np.random.default_rng(M).choice(np.arange(1, m - 1), 6,
                                                                                           replace=False))])
@@ -592,11 +661,14 @@ def test_split_k_down_sampled(big_layer, M, ks):
     _say("split-K M=%d: gate/up %s; down error %.2e, %.3f of the model tolerance" % (M, g, e, d))
 
 
-@pytest.mark.parametrize("M", [100, 190, 333])
-def test_tile_heights_sampled(big_layer, M):
-    """The tiled GEMMs' other tile shapes, each with a ragged last row tile
-    (gate/up heights 64, 96 and 192; down 64 x 128 and 128 x 128 with K
-    splits), oracle-checked on sampled rows, the tile edges included."""
+@pytest.mark.parametrize("M,height,down", [(100, 64, (64, 128, 4, True)), (190, 96, (64, 128, 2, True)),
+                                           (230, 128, (64, 128, 2, True)), (333, 192, (128, 256, 5, False)),
+                                           (400, 256, (128, 256, 4, False))])
+def test_tile_heights_sampled(big_layer, M, height, down):
+    """Each gate/up tile height with a ragged last row tile, and the down tiles
+    that these calls take, oracle-checked on sampled rows, the tile edges
+    included."""
+    _plan_is(M, 4096, 12288, down, height)
     w = synth.Workload(98, "heights", M, 4096, 12288, act="outlier", outlier_ratio=0.01)
     rows = lambda m: np.unique([r for r in (0, 63, 64, 95, 96, 191, 192, m - 1) if r < m])
     g, e, d = _full_size_case(big_layer, w, 0, rows, 0)
@@ -610,7 +682,8 @@ def test_gateup_bytes_do_not_depend_on_the_tile_height(big_layer):
     w = synth.Workload(98, "heights", 700, 4096, 12288, act="outlier", outlier_ratio=0.01)
     x = dev_bf16(synth.make_x(w, layer=1))
     ref = None
-    for M in (700, 512, 333, 256, 190, 65):
+    for M, height in ((700, 192), (512, 256), (333, 192), (256, 128), (190, 96), (65, 64)):
+        _plan_is(M, 4096, 12288, gateup=height)
         xq = torch.empty((M, 4096), dtype=torch.uint8, device=DEV)
         xs = torch.empty((32, M), dtype=torch.float32, device=DEV)
         hq = torch.full((M, 12288), 0xFF, dtype=torch.uint8, device=DEV)
@@ -630,8 +703,9 @@ def test_maximum_h_and_i(M, H, I):
     """The largest H (16384) and the largest I (65536) the library takes, each
     with a small M: long K loops (128 K-groups in the gate/up, 512 in the
     down), and at I = 65536 the down GEMM's widest K split (32 workgroups per
-    output tile, one tile). Every row against the oracle."""
+    output tile). Every row against the oracle."""
     _say("max sizes M=%d H=%d I=%d" % (M, H, I))
+    _plan_is(M, H, I, (64, 128, 32 if I == 65536 else 1, True))
     w = synth.Workload(92, "max_%d_%d" % (H, I), M, H, I, act="outlier", outlier_ratio=0.01)
     lay = Layer(w, layer=1)
     g, e, d = _full_size_case(lay, w, 0, lambda m: np.arange(m), 0)
@@ -672,9 +746,9 @@ def test_maximum_m():
 
 @pytest.mark.parametrize("M", [50, 130])
 def test_tiled_partial_column_tile(M):
-    """The tiled kernels at H = 640 (H % 256 == 128): the down GEMM's last
-    256-column tile holds 128 valid columns (clamped weight rows, the second
-    block scale falling back to the first, columns past N never stored)."""
+    """The tiled kernels at H = 640, a column count that is no multiple of 256,
+    with few rows (the down GEMM takes 64 x 128 tiles; the 256-wide ones' partial
+    column tile is in test_down_tile_shapes)."""
     _say("tiled H=640 M=%d" % M)
     lc.lacache_set_path_policy(2)
     w = synth.Workload(95, "h640", M, 640, 1152, act="outlier", outlier_ratio=0.02)
@@ -690,13 +764,14 @@ def test_tiled_partial_column_tile(M):
 
 
 def test_bm256_partial_row_and_column_tiles():
-    """256-row tiles with both tails: M = 12000 at H = 640, I = 1152 takes
-    256-row tiles in both GEMMs (128-row ones would need more rounds of one
-    workgroup per CU), the last row tile holds 224 rows, and the down GEMM's
-    last 256-column tile holds 128 valid columns. Sampled rows, both tails'
-    rows included, against the oracle."""
+    """Many rows of a narrow layer: M = 12000 at H = 640, I = 1152 takes 256-row
+    gate/up tiles whose last holds 224 rows, and 128 x 128 down tiles whose last
+    row tile holds 96 (256 x 256 down tiles with both tails are in
+    test_down_tile_shapes). Sampled rows, the tails' rows included, against the
+    oracle."""
     M, H, I = 12000, 640, 1152
     _say("bm256 partial row and column tiles M=%d H=%d" % (M, H))
+    _plan_is(M, H, I, (128, 128, 1, False), 256)
     w = synth.Workload(97, "bm256_tails", M, H, I, act="outlier", outlier_ratio=0.02)
     lay = Layer(w, layer=1)
     pick = lambda m: np.unique(np.concatenate([[0, 255, 256, m - 224, m - 2, m - 1],
