@@ -6,9 +6,12 @@
 // scale 0 and codes 0x00; only the set of values sharing a scale changes.
 //
 // A coarse scale needs the max over a whole row (or tensor), which no GEMM
-// tile sees, so these paths quantize in separate passes over an fp32 (or
-// bf16) source: the row maxima, then the scales (a reduction over the rows
-// for a tensor), then the codes. The scales are also written in the GEMMs'
+// tile sees, so these paths quantize from an fp32 (or bf16) source in memory.
+// Per token, one kernel holds a row of up to 16384 values in registers between
+// its maximum and its codes (the normalized activations do not even pass
+// through memory: launch_rmsnorm_quant_token); longer rows, and a tensor, take
+// the row maxima, then the scales (a reduction over the rows for a tensor),
+// then the codes. The scales are also written in the GEMMs'
 // K-group-major layout (every K-group of row m carries row m's scale), so the
 // tiled GEMMs run unchanged; a weight's per-row scales are applied in the
 // GEMM epilogue to each output column.

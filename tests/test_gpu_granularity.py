@@ -20,6 +20,7 @@ import oracle.granularity as G
 import paper_2607_16339_amd as lc
 import synth
 from gpu_util import DEV, SILU_LIP, dev_bf16, host, host_bf16, mfma_dot_bound
+from oracle import csweep
 from oracle.bf16 import bf16_to_f32, rne_bf16
 
 pytestmark = pytest.mark.gpu
@@ -92,6 +93,83 @@ def test_quant_rows_bit_exact(gran, ogran, M, K):
     assert np.array_equal(host(q), rq), "codes differ in %d places" % int((host(q) != rq).sum())
     assert np.array_equal(host(s_rows).view(np.uint32), rs.view(np.uint32))
     assert np.array_equal(host(s_kgm).view(np.uint32), np.tile(rs, (K // 128, 1)).view(np.uint32))
+
+
+@pytest.mark.parametrize("M,K", [(3, 2048), (3, 2176), (5, 4096), (4, 4224), (3, 8192), (2, 12288), (3, 16384),
+                                 (37, 16512)])
+def test_quant_rows_per_token_at_every_row_length(M, K):
+    """One scale per row, held in 1, 2, 4 or 8 passes of a workgroup's registers
+    (K <= 2048, 4096, 8192, 16384; full and partly filled last passes, the
+    maximum in the last values of a row) and, above, in three kernels."""
+    _say("per-token rows M=%d K=%d" % (M, K))
+    rng = np.random.default_rng(M + K)
+    v = (rng.standard_normal((M, K)) * np.exp(rng.uniform(-4, 4, (M, 1)))).astype(np.float32)
+    v[0, :] = 0.0
+    v[1, K - 1] = np.float32(-9e3)
+    q = torch.full((M, K), 0xFF, dtype=torch.uint8, device=DEV)
+    s_kgm = torch.full((K // 128, M), float("nan"), dtype=torch.float32, device=DEV)
+    s_rows = torch.full((M,), float("nan"), dtype=torch.float32, device=DEV)
+    lc.lacache_quant_rows_g(torch.from_numpy(v).to(DEV), q, s_kgm, s_rows, lc.LACACHE_GRAN_TOKEN)
+    torch.cuda.synchronize()
+    rq, rs = G.quantize_rows(v, G.GRAN_TOKEN)
+    assert np.array_equal(host(q), rq), "codes differ in %d places" % int((host(q) != rq).sum())
+    assert np.array_equal(host(s_rows).view(np.uint32), rs.view(np.uint32))
+    assert np.array_equal(host(s_kgm).view(np.uint32), np.tile(rs, (K // 128, 1)).view(np.uint32))
+
+
+def _quantize_any(v):
+    """Codes and scale of each set v[i] (NaN and infinite values included): the
+    scale from the largest magnitude that is not NaN, a NaN quotient clipped to
+    -448, every code 0 where the scale is 0."""
+    with np.errstate(invalid="ignore", over="ignore"):
+        s = (np.fmax.reduce(np.abs(v), axis=1, initial=np.float32(0)) / np.float32(448)).astype(np.float32)
+        u = v / np.where(s == 0, np.float32(1), s)[:, None]
+    u = np.where(np.isnan(u), np.float32(-448), np.clip(u, np.float32(-448), np.float32(448)))
+    codes = csweep.encode_f32(np.ascontiguousarray(u.astype(np.float32)).ravel()).reshape(v.shape)
+    return np.where((s == 0)[:, None], np.uint8(0), codes), s
+
+
+@pytest.mark.parametrize("gran,K", [(lc.LACACHE_GRAN_GROUP, 1024), (lc.LACACHE_GRAN_TOKEN, 1024),
+                                    (lc.LACACHE_GRAN_TOKEN, 12288), (lc.LACACHE_GRAN_TOKEN, 16512),
+                                    (lc.LACACHE_GRAN_TENSOR, 1024)])
+def test_quantizers_on_nans_and_infinities(gran, K):
+    """NaNs are left out of the maximum and take the code of -448; an infinite
+    value makes the scale infinite: itself the code of -448, the others zero.
+    Scales below the fast quantizer's range and the largest magnitudes as well."""
+    _say("quantizer %d on NaNs, K=%d" % (gran, K))
+    csweep.build_csweep()
+    rng = np.random.default_rng(K)
+    M = 12
+    v = rng.standard_normal((M, K)).astype(np.float32)
+    v[1, 3], v[2, K - 1] = np.nan, np.inf
+    v[3, 130], v[3, 131], v[4, :] = -np.inf, np.nan, np.nan
+    v[5, ::7] = np.nan
+    v[6, 64], v[6, 65] = np.float32(3.4e38), np.float32(-0.0)
+    v[7] *= np.float32(1e-40)  # subnormal values and scale
+    v[8] *= np.float32(1e-30)  # the scale is below 2^-100
+    v[9] *= np.float32(1e-36)
+    v[9, 9] = np.nan
+    v.view(np.uint32)[10, 20:24] = [0x7F800001, 0xFF800001, 0xFFC12345, 0x7FFFFFFF]
+    v[11] = np.float32(-0.0)
+    sets = [v] if gran != lc.LACACHE_GRAN_TENSOR else [v, np.where(np.isinf(v), np.float32(2), v)]
+    for x in sets:
+        if gran == lc.LACACHE_GRAN_GROUP:
+            rq, rs = _quantize_any(x.reshape(-1, 128))
+            rq, kgm = rq.reshape(M, K), rs.reshape(M, K // 128).T
+        elif gran == lc.LACACHE_GRAN_TOKEN:
+            rq, rs = _quantize_any(x)
+            kgm = np.tile(rs, (K // 128, 1))
+        else:
+            rq, rs = _quantize_any(x.reshape(1, -1))
+            rq, kgm = rq.reshape(M, K), np.full((K // 128, M), rs[0], dtype=np.float32)
+        q = torch.full((M, K), 0xAA, dtype=torch.uint8, device=DEV)
+        s_kgm = torch.full((K // 128, M), float("nan"), dtype=torch.float32, device=DEV)
+        s_rows = None if gran == lc.LACACHE_GRAN_GROUP else torch.full((M,), 7.0, dtype=torch.float32, device=DEV)
+        lc.lacache_quant_rows_g(torch.from_numpy(x).to(DEV), q, s_kgm, s_rows, gran)
+        torch.cuda.synchronize()
+        assert np.array_equal(host(s_kgm).view(np.uint32), np.ascontiguousarray(kgm).view(np.uint32))
+        bad = np.argwhere(host(q) != rq)
+        assert not len(bad), (bad[:4], host(q)[tuple(bad[0])], rq[tuple(bad[0])])
 
 
 def _row_gemm_bound(aq, a_rows, bq, b_rows, acc_abs):
@@ -188,6 +266,44 @@ def test_fused_call_equals_its_stages(gran, M):
     torch.cuda.synchronize()
     assert torch.equal(fused.view(torch.int16), staged.view(torch.int16))
     assert torch.equal(fused.view(torch.int16), again.view(torch.int16))
+
+
+@pytest.mark.parametrize("M,H,I", [(3, 128, 16512), (40, 640, 2176), (33, 1536, 256), (40, 2176, 256),
+                                   (40, 4096, 4224), (1100, 4096, 256), (1030, 1024, 256), (9, 8192, 8320),
+                                   (5, 16384, 128)])
+def test_per_token_call_equals_its_stages_at_every_row_length(M, H, I):
+    """The one-kernel norm + per-token quantization at 1 to 32 passes, one, two
+    and four wavefronts to a row (and one to a row above 1024 rows, four rows to
+    a workgroup), and h rows of every length class: the fused call is the staged
+    one bit for bit, whose norm and quantizer have oracles."""
+    _say("per-token M=%d H=%d I=%d" % (M, H, I))
+    gran = lc.LACACHE_GRAN_TOKEN
+    x, nw, wgu, wd = _inputs(M, H, I, seed=M + H)
+    x[0] = 0
+    wgu_q, wgu_s, wgu_rs = _weights(wgu, gran)
+    wd_q, wd_s, wd_rs = _weights(wd, gran)
+    xd, nwd = dev_bf16(x), dev_bf16(nw)
+    fused = torch.empty((M, H), dtype=torch.bfloat16, device=DEV)
+    lc.lacache_ffn_fp8_g(xd, nwd, wgu_q, wgu_s, wgu_rs, wd_q, wd_s, wd_rs, fused, gran)
+    y = torch.empty((M, H), dtype=torch.float32, device=DEV)
+    xq = torch.empty((M, H), dtype=torch.uint8, device=DEV)
+    xs = torch.empty((H // 128, M), dtype=torch.float32, device=DEV)
+    r = torch.empty((M,), dtype=torch.float32, device=DEV)
+    h = torch.empty((M, I), dtype=torch.float32, device=DEV)
+    hq = torch.empty((M, I), dtype=torch.uint8, device=DEV)
+    hs = torch.empty((I // 128, M), dtype=torch.float32, device=DEV)
+    staged = torch.empty((M, H), dtype=torch.bfloat16, device=DEV)
+    lc.lacache_rmsnorm_f32(xd, nwd, y)
+    lc.lacache_quant_rows_g(y, xq, xs, r, gran)
+    lc.lacache_gateup_swiglu_f32(xq, xs, wgu_q, wgu_s, wgu_rs, h)
+    torch.cuda.synchronize()
+    rows = np.unique([0, 1, M // 2, M - 1])
+    rq, rs = G.quantize_rows(O.rmsnorm(x[rows], nw)[0], G.GRAN_TOKEN)
+    assert np.array_equal(host(xq)[rows], rq) and np.array_equal(host(r)[rows].view(np.uint32), rs.view(np.uint32))
+    lc.lacache_quant_rows_g(h, hq, hs, r, gran)
+    lc.lacache_down_proj_g(hq, hs, wd_q, wd_s, wd_rs, staged)
+    torch.cuda.synchronize()
+    assert torch.equal(fused.view(torch.int16), staged.view(torch.int16))
 
 
 def test_group_granularity_is_the_library_ffn():
