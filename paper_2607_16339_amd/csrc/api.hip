@@ -111,7 +111,7 @@ int choose_path(int64_t M, int64_t H, int64_t I, Path* p) {
 // or the split-K partials of the tiled down GEMM, whichever path runs (both
 // are possible at small M: by shape and by the path policy).
 size_t scratch_bytes(int64_t M, int64_t H, int64_t I) {
-  const size_t sk = M <= kSkinnyMaxM ? skinny_gateup_ws_bytes(M, I) : 0;
+  const size_t sk = M <= kSkinnyMaxM ? skinny_gateup_ws_bytes(M, H, I) : 0;
   const size_t tl = tiled_down_ws_bytes(M, H, I);
   return sk > tl ? sk : tl;
 }
@@ -329,7 +329,7 @@ int lacache_gateup_swiglu_quant(void* stream, const uint8_t* xq, const float* xs
     return LACACHE_ERR_INVALID_ARG;
   hipStream_t st = static_cast<hipStream_t>(stream);
   void* skinny = nullptr;
-  if (path == Path::kSkinny) RETURN_IF(get_workspace(st, skinny_gateup_ws_bytes(M, I), &skinny));
+  if (path == Path::kSkinny) RETURN_IF(get_workspace(st, skinny_gateup_ws_bytes(M, H, I), &skinny));
   return run_gateup(st, path, xq, xs, wgu_q, wgu_s, hq, hs, h_tap, M, H, I, skinny);
 }
 
@@ -613,7 +613,7 @@ int lacache_rope_scatter(void* stream, const uint16_t* qkv, const int32_t* rows,
 
 size_t lacache_first_layer_workspace_bytes(int64_t R, int64_t heads, int64_t H) {
   if (R < 0 || heads <= 0 || check_dim(H, kMaxH) != LACACHE_OK) return 0;
-  return align256(static_cast<size_t>(R * H) * 2) + align256(static_cast<size_t>(R * 3 * heads * 128) * 2);
+  return align256(static_cast<size_t>(R * H) * 2) + align256(static_cast<size_t>(R) * 4);  // y, the positions
 }
 
 int lacache_first_layer_tokens(void* stream, const int32_t* token_ids, const int32_t* rows, int64_t R,

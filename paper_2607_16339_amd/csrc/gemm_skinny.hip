@@ -533,10 +533,9 @@ bool skinny_supported(int64_t M, int64_t H, int64_t I) {
   return M >= 1 && M <= kSkinnyMaxM && gateup_v_ok(M, H) && down_ok(M, I);
 }
 
-size_t skinny_gateup_ws_bytes(int64_t M, int64_t I) {
-  // h [M x I] fp32, or for 33..64 rows the two K halves' gate and up sums [2][M][2I]
-  // (not needed where all of K fits)
-  const size_t n = static_cast<size_t>(M) * static_cast<size_t>(I) * (M <= 32 ? 1 : 4);
+size_t skinny_gateup_ws_bytes(int64_t M, int64_t H, int64_t I) {
+  // h [M x I] fp32, or the two K halves' gate and up sums [2][M][2I]
+  const size_t n = static_cast<size_t>(M) * static_cast<size_t>(I) * (gateup_halves(M, H) == 1 ? 1 : 4);
   return ((n * sizeof(float) + 255) / 256) * 256;
 }
 

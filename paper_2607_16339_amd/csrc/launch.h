@@ -96,7 +96,7 @@ hipError_t launch_down_rows64(hipStream_t st, const uint8_t* hq, const float* hs
 // (no initial contents) for h; the down stage needs none.
 constexpr int64_t kSkinnyMaxM = 64;
 bool skinny_supported(int64_t M, int64_t H, int64_t I);
-size_t skinny_gateup_ws_bytes(int64_t M, int64_t I);
+size_t skinny_gateup_ws_bytes(int64_t M, int64_t H, int64_t I);
 hipError_t launch_gateup_skinny(hipStream_t st, const uint8_t* xq, const float* xs, const uint8_t* wq,
                                 const float* ws, uint8_t* hq, float* hs, float* h_tap, int64_t M, int64_t H,
                                 int64_t I, void* ws_buf);

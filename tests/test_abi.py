@@ -219,6 +219,10 @@ def test_workspace_bytes_and_status_strings(L):
     assert L.lacache_ffn_workspace_bytes(64, H, I, 128) == (
         max(a256(2 * 64 * 2 * I * 4), a256(6 * 64 * H * 4)) + a256(64 * H) + a256(H // 128 * 64 * 4)
         + a256(64 * I) + a256(I // 128 * 64 * 4))
+    # (where all of K fits the LDS, h alone: H = 2048 at 64 rows, 2688 at 48)
+    for m, hh, n in ((64, 2048, 1), (64, 2176, 4), (48, 2688, 1), (48, 2816, 4), (33, 2560, 1)):
+        assert L.lacache_ffn_workspace_bytes(m, hh, 512, 128) == (
+            a256(n * m * 512 * 4) + a256(m * hh) + a256(hh // 128 * m * 4) + a256(m * 512) + a256(4 * m * 4))
     want = scratch + a256(M * H) + a256(H // 128 * M * 4) + a256(M * I) + a256(I // 128 * M * 4)
     assert L.lacache_ffn_workspace_bytes(M, H, I, 128) == want
     M = 512
@@ -346,6 +350,8 @@ def test_first_layer_validation(L):
         == INVALID
     assert L.lacache_first_layer_tokens(None, ids, rows, 0, emb, 100, nw, wq, cs, sn, cache, q, k, v, 2, 64, 256) == OK
     assert L.lacache_first_layer_workspace_bytes(32, 32, 4096) > 0
+    # the normalized rows and their positions, nothing else
+    assert L.lacache_first_layer_workspace_bytes(1000, 32, 4096) == 1000 * 4096 * 2 + 4096
 
 
 def test_weight_tile_layout_helpers():
