@@ -399,6 +399,9 @@ int lacache_embed_rmsnorm(void* stream, const int32_t* token_ids, const int32_t*
  * row the same bytes, so a row's result does not depend on M. */
 int lacache_linear_bf16(void* stream, const uint16_t* a, const uint16_t* w, uint16_t* out, float* out_tap, int64_t M,
                         int64_t N, int64_t K);
+/* Test hook: the output tile (rows, columns) that a workgroup of such a call
+ * takes on the current device. M > 0. Launches nothing. */
+int lacache_linear_tile(int64_t M, int64_t N, int64_t K, int* tile);
 
 /*
  * RoPE and scatter: row r of qkv ([R x 3 heads 128] bf16, columns = Q heads,

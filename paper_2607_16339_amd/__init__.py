@@ -322,6 +322,13 @@ def lacache_tiled_plan(M, H, I, col_scales=False):
     return plan[0], plan[1], plan[2], plan[3], bool(plan[4])
 
 
+def lacache_linear_tile(M, N, K):
+    """(rows, columns) of the output tiles of the bf16 projection for a call of these sizes."""
+    tile = (ctypes.c_int * 2)()
+    check(lib().lacache_linear_tile(M, N, K, tile), "lacache_linear_tile")
+    return tile[0], tile[1]
+
+
 def lacache_status_string(status):
     return status_string(status)
 

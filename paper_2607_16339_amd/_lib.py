@@ -50,6 +50,7 @@ SIGNATURES = {
                                         _I64]),
     "lacache_first_layer_workspace_bytes": (ctypes.c_size_t, [_I64, _I64, _I64]),
     "lacache_set_path_policy": (_I, [_I]),
+    "lacache_linear_tile": (_I, [_I64, _I64, _I64, _P]),
     "lacache_tiled_plan": (_I, [_I64, _I64, _I64, _I, _P]),
     "lacache_status_string": (ctypes.c_char_p, [_I]),
     "lacache_release_workspace": (None, []),

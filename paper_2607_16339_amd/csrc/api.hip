@@ -597,6 +597,17 @@ int lacache_linear_bf16(void* stream, const uint16_t* a, const uint16_t* w, uint
   return hip_status(launch_linear_bf16(static_cast<hipStream_t>(stream), a, w, out, out_tap, M, N, K));
 }
 
+int lacache_linear_tile(int64_t M, int64_t N, int64_t K, int* tile) {
+  RETURN_IF(check_m(M));
+  RETURN_IF(check_dim(N, kMaxN));
+  RETURN_IF(check_dim(K, kMaxN));
+  if (M == 0 || tile == nullptr) return LACACHE_ERR_INVALID_ARG;
+  int t[2];
+  linear_tile(M, N, K, t);
+  std::memcpy(tile, t, sizeof(t));
+  return LACACHE_OK;
+}
+
 int lacache_rope_scatter(void* stream, const uint16_t* qkv, const int32_t* rows, int64_t R, const float* rope_cos,
                          const float* rope_sin, uint16_t* q, uint16_t* k, uint16_t* v, int64_t heads, int64_t N) {
   if (R < 0 || heads <= 0 || N <= 0) return LACACHE_ERR_INVALID_ARG;

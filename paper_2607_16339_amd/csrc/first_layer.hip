@@ -617,19 +617,49 @@ hipError_t launch_embed_rmsnorm(hipStream_t st, const int32_t* ids, const int32_
 
 namespace {
 
+struct LinTile {
+  int bm, bn;
+};
+// The tile of the least time for more than kLinTiledMinM rows: rounds of one
+// workgroup per CU of a start and end and K/64 K-steps, and a K-step's time that
+// grows with the work in flight. Fitted at 126 sizes, M = 129..4096, N x K = 1536 x
+// 512 to 24576 x 8192 and 12288 x 128 to 4096, all tiles in turn in one process: on
+// average 0.05 % slower than the best tile, 3.7 % at most (rounds times one cost per
+// tile, as fitted at K = 4096 alone, 1.6 % and 37 %: N = 12288, K = 128, M = 1280 30.1
+// us on 256 x 192 tiles, 22.0 on 128 x 128). At N = 12288, K = 4096, in us on 128 x
+// 128, 128 x 192 and 256 x 192 tiles: M = 256 43, 54, 74; 512 78, 58, 75; 768 110,
+// 104, 79; 1000 121, 115, 90.
+LinTile lin_tile(int64_t M, int64_t N, int64_t K) {
+  struct Tile {
+    int bm, bn;
+    double start, c0, c1;
+  };
+  constexpr Tile kTiles[3] = {{128, 128, 3.4, 0.43, 0.12}, {128, 192, 5.1, 0.60, 0.18}, {256, 192, 11.0, 0.75, 0.42}};
+  const int64_t cus = device_cu_count();
+  const double ks = static_cast<double>(K) / 64.0;
+  LinTile pick{128, 128};
+  double best = 0.0;
+  for (int t = 0; t < 3; ++t) {
+    const Tile& s = kTiles[t];
+    if (N % s.bn != 0) continue;  // (N is a multiple of 128)
+    const int64_t items = ((M + s.bm - 1) / s.bm) * (N / s.bn);
+    const double rounds = static_cast<double>((items + cus - 1) / cus);
+    const double us = rounds * (s.start + s.c0 * ks) + s.c1 * ks * static_cast<double>(items) / static_cast<double>(cus);
+    if (t == 0 || us < best) pick = {s.bm, s.bn}, best = us;
+  }
+  return pick;
+}
+
+// Up to 128 rows: three weight slabs per workgroup when that still gives a
+// workgroup per CU (few rows), else one.
+bool lin_wide(int64_t M, int64_t N) { return M <= 32 && N % 48 == 0 && N / 48 >= 256; }
+
 template <bool kRope>
 hipError_t launch_linear(hipStream_t st, const uint16_t* a, const uint16_t* w, uint16_t* out, float* out_tap, int64_t M,
                          int64_t N, int64_t K, const RopeArgs& ra) {
   if (M > kLinTiledMinM) {
-    // The tile with the least rounds x cost, the cost of a round in units of a
-    // 128 x 128 one as measured at N = 12288, K = 4096 (one round: 43 us at
-    // 128 x 128, 57 at 128 x 192, 84 at 256 x 192): M = 256 runs in 43 us, 512 in
-    // 60, 768 in 80 and 1000 in 91 (113 and 119 with 128-row tiles alone)
+    const LinTile tile = lin_tile(M, N, K);
     const int64_t cus = device_cu_count();
-    auto cost = [&](int64_t bm, int64_t bn, int64_t unit) {
-      return N % bn != 0 ? INT64_MAX : (((M + bm - 1) / bm) * (N / bn) + cus - 1) / cus * unit;
-    };
-    const int64_t c0 = cost(128, 128, 20), c1 = cost(128, 192, 27), c2 = cost(256, 192, 39);
 #define LT(BM_, BN_, PING_)                                                                                       \
   do {                                                                                                           \
     const int r_ = static_cast<int>((M + BM_ - 1) / BM_), c_ = static_cast<int>(N / BN_);                        \
@@ -637,21 +667,19 @@ hipError_t launch_linear(hipStream_t st, const uint16_t* a, const uint16_t* w, u
                        dim3(static_cast<unsigned>(static_cast<int64_t>(r_) * c_ < cus ? r_ * c_ : cus)),         \
                        dim3(kLtWaves * 64), 0, st, a, w, out, out_tap, M, N, K, r_, c_, ra);                         \
   } while (0)
-    if (c2 < c0 && c2 < c1)
+    if (tile.bm == 256)
       LT(256, 192, true);
-    else if (c1 < c0)
+    else if (tile.bn == 192)
       LT(128, 192, false);
     else
       LT(128, 128, false);
 #undef LT
     return hipGetLastError();
   }
-  // up to 64 rows per pass; the last pass may hold fewer slabs. Three weight
-  // slabs per workgroup when that still gives a workgroup per CU (few rows),
-  // else one.
+  // up to 64 rows per pass; the last pass may hold fewer slabs
   const unsigned passes = static_cast<unsigned>((M + 63) / 64);
   const int mt = static_cast<int>(M >= 64 ? 4 : (M + 15) / 16);
-  const bool wide = mt <= 2 && N % 48 == 0 && N / 48 >= 256;
+  const bool wide = lin_wide(M, N);
   const dim3 grid(static_cast<unsigned>(N / (wide ? 48 : 16)), passes), block(kLinSplit * 64);
 #define LB(MT_, NJ_) hipLaunchKernelGGL((linear_bf16_kernel<MT_, NJ_, kRope>), grid, block, 0, st, a, w, out, out_tap, M, N, K, ra)
   if (wide) {
@@ -666,6 +694,15 @@ hipError_t launch_linear(hipStream_t st, const uint16_t* a, const uint16_t* w, u
 }
 
 }  // namespace
+
+void linear_tile(int64_t M, int64_t N, int64_t K, int (&tile)[2]) {
+  if (M > kLinTiledMinM) {
+    const LinTile t = lin_tile(M, N, K);
+    tile[0] = t.bm, tile[1] = t.bn;
+  } else {
+    tile[0] = 64, tile[1] = lin_wide(M, N) ? 48 : 16;
+  }
+}
 
 hipError_t launch_linear_bf16(hipStream_t st, const uint16_t* a, const uint16_t* w, uint16_t* out, float* out_tap,
                               int64_t M, int64_t N, int64_t K) {

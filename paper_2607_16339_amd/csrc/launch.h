@@ -110,6 +110,8 @@ hipError_t launch_embed_rmsnorm(hipStream_t st, const int32_t* ids, const int32_
                                 uint16_t* y, int64_t H, int32_t* dst = nullptr);
 hipError_t launch_linear_bf16(hipStream_t st, const uint16_t* a, const uint16_t* w, uint16_t* out, float* out_tap,
                               int64_t M, int64_t N, int64_t K);
+// The output tile of the call above: rows and columns of a workgroup.
+void linear_tile(int64_t M, int64_t N, int64_t K, int (&tile)[2]);
 // q, k, v rows of RoPE(y w_qkv^T) (rows [R], w_qkv [3 heads 128 x H]): the
 // bytes of launch_linear_bf16 followed by launch_rope_scatter, in one kernel.
 hipError_t launch_linear_rope(hipStream_t st, const uint16_t* y, const uint16_t* w_qkv, const int32_t* rows, int64_t R,

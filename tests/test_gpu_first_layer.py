@@ -78,6 +78,12 @@ def test_invalid_ids_and_rows_are_skipped():
     assert np.all(c[[1, 2]] == 0x7FC0) and np.all(yy[[1, 2, 3]] == 0x7FC0)
 
 
+def _tile_is(M, N, K, tile):
+    """The projection takes the tile the test is about (a rule that counts compute units)."""
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert lc.lacache_linear_tile(M, N, K) == tile
+
+
 def _linear_check(a, w, out, tap):
     af = bf16_to_f32(a).astype(np.float64)
     wf = bf16_to_f32(w).astype(np.float64)
@@ -106,16 +112,17 @@ def test_linear_bf16(M, N, K):
     _linear_check(a, w, out, tap)
 
 
-@pytest.mark.parametrize("M,N,K", [(300, 384, 1024), (129, 256, 384), (257, 128, 128), (512, 12288, 4096),
-                                   (700, 12288, 512)])
-def test_linear_tiled_equals_streaming(M, N, K):
-    """Above 128 rows the projection runs on 128 x 128 or 128 x 192 tiles (the
-    latter at N = 12288 with 512 and 700 rows); below, W is streamed per 64
-    rows. Both must give every row the same bytes (the same
+@pytest.mark.parametrize("M,N,K,tile", [(300, 384, 1024, (128, 128)), (129, 256, 384, (128, 128)),
+                                        (257, 128, 128, (128, 128)), (512, 12288, 4096, (128, 192)),
+                                        (300, 12288, 128, (128, 192)), (700, 12288, 512, (256, 192))])
+def test_linear_tiled_equals_streaming(M, N, K, tile):
+    """Above 128 rows the projection runs on 128 x 128, 128 x 192 or 256 x 192
+    tiles; below, W is streamed per 64 rows. All must give every row the same bytes (the same
     K quarters, MFMA chains and quarter order), so the same rows through the
     streaming kernel (calls of at most 64 rows) equal the tiled call bit for
     bit, including ragged M, K-step counts not divisible by four and empty
     quarters (K = 128)."""
+    _tile_is(M, N, K, tile)
     rng = np.random.default_rng(M + N + K)
     a = to_bf16_bits(rng.standard_normal((M, K)).astype(np.float32))
     w = to_bf16_bits((0.03 * rng.standard_normal((N, K))).astype(np.float32))
@@ -136,12 +143,14 @@ def test_linear_tiled_equals_streaming(M, N, K):
         _linear_check(a, w, out, tap)
 
 
-@pytest.mark.parametrize("M,K", [(769, 128), (769, 384), (1000, 640)])
-def test_linear_256_row_tiles_equal_streaming(M, K):
-    """256 x 192 tiles (the choice at N = 12288 above 512 rows): a last row
-    tile of one valid row, K quarters that are empty (K = 128) or of unequal
-    length (K = 384, 640), byte for byte the streaming kernel's result."""
+@pytest.mark.parametrize("M,K,tile", [(641, 128, (256, 192)), (769, 128, (128, 192)), (769, 384, (256, 192)),
+                                      (1000, 640, (256, 192))])
+def test_linear_256_row_tiles_equal_streaming(M, K, tile):
+    """256 x 192 tiles (128 x 192 at K = 128, M = 769): a last row tile of one
+    valid row, K quarters that are empty (K = 128) or of unequal length (K = 384,
+    640), byte for byte the streaming kernel's result."""
     N = 12288
+    _tile_is(M, N, K, tile)
     rng = np.random.default_rng(M + K)
     a = to_bf16_bits(rng.standard_normal((M, K)).astype(np.float32))
     w = to_bf16_bits((0.03 * rng.standard_normal((N, K))).astype(np.float32))
@@ -150,7 +159,7 @@ def test_linear_256_row_tiles_equal_streaming(M, K):
     out = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
     tap = torch.full((M, N), float("nan"), dtype=torch.float32, device=DEV)
     lc.lacache_linear_bf16(da, dw, out, tap)
-    rows = [0, 255, 256, 511, 512, 767, 768, M - 1]
+    rows = [0, 255, 256, 511, 512, 640, min(M - 1, 768), M - 1]
     out_s = torch.empty((len(rows), N), dtype=torch.bfloat16, device=DEV)
     tap_s = torch.empty((len(rows), N), dtype=torch.float32, device=DEV)
     ri = torch.tensor(rows, device=DEV)
@@ -289,11 +298,11 @@ def test_fused_rope_epilogue_equals_the_stages(R, heads, H):
     assert not torch.isnan(fused[1][:, rows[-1]].float()).any()
 
 
-@pytest.mark.parametrize("R,heads,H", [(9, 2, 256), (40, 32, 256), (300, 2, 128), (300, 32, 128), (1000, 32, 128)])
+@pytest.mark.parametrize("R,heads,H", [(9, 2, 256), (40, 32, 256), (300, 2, 128), (300, 32, 128), (700, 32, 128)])
 def test_invalid_ids_write_nothing_in_the_fused_call(R, heads, H):
     """An entry whose token id is outside the vocabulary writes no row of any
     cache, on the streaming kernel (9, 40 rows) and on every tile shape (300
-    and 1000), whatever an earlier call left in the workspace."""
+    and 700), whatever an earlier call left in the workspace."""
     N, vocab = R + 3, 100
     rng, embed, nw, wqkv, cos_t, sin_t = _setup(H, heads, N, vocab, seed=R + heads)
     ids = rng.integers(0, vocab, R)
@@ -314,7 +323,7 @@ def test_invalid_ids_write_nothing_in_the_fused_call(R, heads, H):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
 
 
-@pytest.mark.parametrize("R,heads,H", [(5, 2, 256), (300, 2, 128), (300, 32, 128), (1000, 32, 128)])
+@pytest.mark.parametrize("R,heads,H", [(5, 2, 256), (300, 2, 128), (300, 32, 128), (700, 32, 128)])
 def test_nans_are_stored_as_one_pattern(R, heads, H):
     """A NaN of the norm, the projection or RoPE is stored as the quiet NaN
     0x7FC0, whatever the sign and payload of the embedding's, the weights' or the

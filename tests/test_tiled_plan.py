@@ -46,3 +46,19 @@ def test_plan_arguments():
     assert L.lacache_tiled_plan(64, 100, 128, 0, p) == lc.LACACHE_ERR_INVALID_ARG
     assert L.lacache_tiled_plan(64, 1 << 20, 128, 0, p) == lc.LACACHE_ERR_UNSUPPORTED
     assert L.lacache_tiled_plan(64, 128, 128, 0, p) == lc.LACACHE_OK
+
+
+def test_projection_tiles():
+    """Streamed up to 128 rows (three slabs to a workgroup where one per CU
+    remains), and each of the three tile shapes above."""
+    if not torch.cuda.is_available():
+        for size, tile in (((32, 12288, 4096), (64, 48)), ((33, 12288, 4096), (64, 16)), ((128, 384, 128), (64, 16)),
+                           ((129, 12288, 4096), (128, 128)), ((512, 12288, 4096), (128, 192)),
+                           ((1000, 12288, 4096), (256, 192)), ((1280, 12288, 128), (128, 128)),
+                           ((1 << 24, 128, 128), (128, 128))):
+            assert lc.lacache_linear_tile(*size) == tile, size
+    t = (ctypes.c_int * 2)()
+    L = _lib.lib()
+    assert L.lacache_linear_tile(0, 128, 128, t) == lc.LACACHE_ERR_INVALID_ARG
+    assert L.lacache_linear_tile(1, 128, 128, None) == lc.LACACHE_ERR_INVALID_ARG
+    assert L.lacache_linear_tile(1, 100, 128, t) == lc.LACACHE_ERR_INVALID_ARG
