@@ -160,6 +160,22 @@ __device__ __forceinline__ v4f mfma_fp8_16x16x128(v8i a, v8i b, v4f c) {
   return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 0, 0, 0, 0, 0, 0);
 }
 
+typedef unsigned int u4v __attribute__((ext_vector_type(4)));
+// An MFMA operand from its two 16-byte chunks.
+__device__ __forceinline__ v8i cat_frag(u4v lo, u4v hi) {
+  v8i f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    f[i] = static_cast<int>(lo[i]);
+    f[4 + i] = static_cast<int>(hi[i]);
+  }
+  return f;
+}
+// Tiles of fp8 rows lie in LDS as [rows][128 bytes], the eight 16-byte chunks of
+// a row permuted by an xor with (row / 2) mod 8, which spreads the 16 rows of an
+// operand read over the banks.
+__device__ __forceinline__ int swz(int row) { return (row >> 1) & 7; }
+
 // An int the compiler can see is the same in every lane of the wavefront.
 __device__ __forceinline__ int wave_uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 

@@ -18,10 +18,11 @@
 // The products, scales and the order of an element's K-groups are those of the
 // tiled kernel: the same bits for the same K splits.
 //
-// Against the tiled kernel's 64 x 128 tiles, whole FFN in sequence with weights
-// from memory: H = 4096, I = 12288, M = 128 62.1 -> 61.3 us; H = 3072, I = 8192,
-// M = 180 42.0 -> 40.2; H = 2048, I = 6144, M = 256 32.4 -> 31.2; H = 7168, I =
-// 2048, M = 200 52.8 -> 51.3; H = 1024, I = 3072, M = 160 26.3 -> 25.4. The same
+// Against the tiled kernel's 64 x 128 tiles over the same K splits, whole FFN in
+// sequence with weights from memory, in us: H = 4096, I = 12288, M = 96 59.2 ->
+// 57.9, 128 60.4 and 60.4, 256 72.5 -> 70.3; H = 3072, I = 8192, M = 180 40.9 ->
+// 38.3, 512 60.9 -> 58.5; H = 2048, I = 6144, M = 256 31.8 -> 30.5; H = 7168, I =
+// 2048, M = 190 51.9 -> 50.5; H = 1024, I = 3072, M = 150 25.8 -> 24.6. The same
 // scheme for the gate/up GEMM (two slabs per wavefront) gained nothing: 100 MB
 // over 96 column tiles stream in 24.7 us with no products at all (192 tiles that
 // share no weights: 19.3), and the tiled kernel's loop hides under that.
@@ -39,21 +40,6 @@ constexpr int kChunk = 4;        // K-groups per chunk
 constexpr int kRing = 3;         // chunks in the ring
 constexpr int kMaxGroups = 128;  // K-groups of a split, at most (block scales in LDS)
 constexpr int kThreads = (kMul + kCopiers) * 64;
-
-typedef unsigned int u4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ v8i cat(u4 lo, u4 hi) {
-  v8i f;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    f[i] = static_cast<int>(lo[i]);
-    f[4 + i] = static_cast<int>(hi[i]);
-  }
-  return f;
-}
-// 16-byte chunk of a 128-byte row as it lies in LDS (operand reads of 16 rows
-// then spread over the banks)
-__device__ __forceinline__ int swizzle(int row, int chunk) { return chunk ^ ((row >> 1) & 7); }
 
 __global__ __launch_bounds__(kThreads) void down_rows64_kernel(
     const uint8_t* __restrict__ hq, const float* __restrict__ hs,  // [M x I] codes, [I/128 x M] scales
@@ -88,7 +74,7 @@ __global__ __launch_bounds__(kThreads) void down_rows64_kernel(
     for (int u = 0; u < 4; ++u) {
       const int row = 8 * (4 * cw + u) + (lane >> 3);
       a_off[u] = static_cast<uint32_t>(row < alim ? row : alim) * static_cast<uint32_t>(I) +
-                 (swizzle(row, lane & 7) << 4);
+                 (((lane & 7) ^ swz(row)) << 4);
     }
     const uint32_t x_off = static_cast<uint32_t>(lane < alim ? lane : alim) * 4;
     const uint8_t* a_base = hq + static_cast<int64_t>(m0) * I + static_cast<int64_t>(kb0) * 128;
@@ -127,11 +113,11 @@ __global__ __launch_bounds__(kThreads) void down_rows64_kernel(
   const int64_t row0 = static_cast<int64_t>(ct) * 128 + 16 * wave;  // this wavefront's weight rows
   const uint8_t* wp = wq + wtile_off(row0, 0, I) + static_cast<int64_t>(kb0) * 2048;
   const uint32_t w_off = static_cast<uint32_t>(lr * 64 + 16 * q);
-  u4 wr[kChunk][2];
+  u4v wr[kChunk][2];
   auto load_w = [&](int j, int slot) {
     const uint8_t* base = wp + static_cast<int64_t>(j < nkb ? j : nkb - 1) * 2048;
-    wr[slot][0] = *reinterpret_cast<const u4*>(base + w_off);
-    wr[slot][1] = *reinterpret_cast<const u4*>(base + w_off + 1024);
+    wr[slot][0] = *reinterpret_cast<const u4v*>(base + w_off);
+    wr[slot][1] = *reinterpret_cast<const u4v*>(base + w_off + 1024);
   };
 #pragma unroll
   for (int u = 0; u < kChunk; ++u) load_w(u, u);
@@ -149,8 +135,8 @@ __global__ __launch_bounds__(kThreads) void down_rows64_kernel(
   auto read_a = [&](int slot, int s) {
     const int u = s / kMT, row = 16 * (s % kMT) + lr;
     const uint8_t* tile = &ring[slot][u][row * 128];
-    af[s % (kAhead + 1)] = cat(*reinterpret_cast<const u4*>(tile + (swizzle(row, q) << 4)),
-                               *reinterpret_cast<const u4*>(tile + (swizzle(row, 4 + q) << 4)));
+    af[s % (kAhead + 1)] = cat_frag(*reinterpret_cast<const u4v*>(tile + ((q ^ swz(row)) << 4)),
+                               *reinterpret_cast<const u4v*>(tile + (((4 + q) ^ swz(row)) << 4)));
     xr[s % (kAhead + 1)] = sXs[slot][u][row];
   };
   auto group = [&](int c, int s) {
@@ -158,7 +144,7 @@ __global__ __launch_bounds__(kThreads) void down_rows64_kernel(
     if (i == 0) w = sWs[c * kChunk + u];
     if (s + kAhead < kChunk * kMT) read_a(c % kRing, s + kAhead);
     const v4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
-    const v4f p = mfma_fp8_16x16x128(cat(wr[u][0], wr[u][1]), af[s % (kAhead + 1)], zero);
+    const v4f p = mfma_fp8_16x16x128(cat_frag(wr[u][0], wr[u][1]), af[s % (kAhead + 1)], zero);
     const float sc = xr[s % (kAhead + 1)] * w;
 #pragma unroll
     for (int r = 0; r < 4; ++r) acc[i][r] = __builtin_fmaf(p[r], sc, acc[i][r]);

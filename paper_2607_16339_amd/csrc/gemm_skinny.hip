@@ -46,16 +46,9 @@ constexpr bool kRotateK = LACACHE_SKINNY_ROT != 0;
 // than direct-to-LDS copies, and a CU pulls about twice as many bytes per
 // second from L2 into registers as into LDS, so the activation operand
 // (re-read by every workgroup) does not slow the weight stream either.
-typedef unsigned int u4v __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ u4v ld_nt(const uint8_t* p) {
   return __builtin_nontemporal_load(reinterpret_cast<const u4v*>(p));
-}
-__device__ __forceinline__ v8i cat_frag(u4v lo, u4v hi) {
-  v8i f;
-  f[0] = static_cast<int>(lo[0]); f[1] = static_cast<int>(lo[1]); f[2] = static_cast<int>(lo[2]); f[3] = static_cast<int>(lo[3]);
-  f[4] = static_cast<int>(hi[0]); f[5] = static_cast<int>(hi[1]); f[6] = static_cast<int>(hi[2]); f[7] = static_cast<int>(hi[3]);
-  return f;
 }
 
 // gate/up: a workgroup owns PAIRS (gate, up) slab pairs; each pair's K

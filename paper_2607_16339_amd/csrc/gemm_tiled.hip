@@ -42,21 +42,13 @@
 namespace lacache {
 namespace {
 
-// LDS tiles are [rows][128 bytes]; the eight 16-byte chunks of a row are
-// permuted by an xor with (row / 2) mod 8, which spreads the 16 rows of an
-// MFMA operand read over the banks.
-__device__ __forceinline__ int swz(int row) { return (row >> 1) & 7; }
 __device__ __forceinline__ int lds_off(int row, int chunk) { return row * 128 + ((chunk ^ swz(row)) << 4); }
 
 // MFMA operand for one 16-row slab: lane (q = l/16, r = l%16) takes row
 // base + r, logical chunks q and 4 + q (the same K placement for A and B).
 __device__ __forceinline__ v8i load_frag(const uint8_t* tile, int row, int q) {
-  const uint4 lo = *reinterpret_cast<const uint4*>(tile + lds_off(row, q));
-  const uint4 hi = *reinterpret_cast<const uint4*>(tile + lds_off(row, 4 + q));
-  v8i f;
-  f[0] = static_cast<int>(lo.x); f[1] = static_cast<int>(lo.y); f[2] = static_cast<int>(lo.z); f[3] = static_cast<int>(lo.w);
-  f[4] = static_cast<int>(hi.x); f[5] = static_cast<int>(hi.y); f[6] = static_cast<int>(hi.z); f[7] = static_cast<int>(hi.w);
-  return f;
+  return cat_frag(*reinterpret_cast<const u4v*>(tile + lds_off(row, q)),
+                  *reinterpret_cast<const u4v*>(tile + lds_off(row, 4 + q)));
 }
 
 // One LDS stage: A tile, B tile, BM activation scales, the two weight-block
@@ -79,22 +71,13 @@ struct Item {
 };
 
 // Item w of R x C tiles x KS splits (R C KS < 2^31). The splits count as
-// extra row tiles (split-major), so the XCD-grouped order of xcd_grouped_tile
-// (here in 32-bit arithmetic) keeps items that share an operand (the same K
-// range of the same rows or columns) on one XCD.
+// extra row tiles (split-major), so the XCD-grouped order keeps items that share
+// an operand (the same K range of the same rows or columns) on one XCD.
 __device__ __forceinline__ Item item_at(int w, int R, int C, int KS, int KB, int BM) {
-  const int RV = R * KS, T = RV * C;
-  const int x = w % static_cast<int>(kXcds), slot = w / static_cast<int>(kXcds);
-  const int per = T / static_cast<int>(kXcds), rem = T % static_cast<int>(kXcds);
-  const int tt = (x < rem ? x * (per + 1) : rem * (per + 1) + (x - rem) * per) + slot;
-  const int gsz = static_cast<int>(kTileGroupRows) * C;
-  const int g = tt / gsz;
-  const int first = g * static_cast<int>(kTileGroupRows);
-  const int rows = RV - first < static_cast<int>(kTileGroupRows) ? RV - first : static_cast<int>(kTileGroupRows);
-  const int wi = tt - g * gsz;
-  const int vr = first + wi % rows;
+  int vr, col;
+  xcd_grouped_tile(w, R * KS, C, vr, col);
   Item it;
-  it.col = wi / rows;
+  it.col = col;
   it.split = vr / R;
   it.m0 = (vr - it.split * R) * BM;
   it.kb0 = it.split * KB / KS;
@@ -588,8 +571,8 @@ constexpr DownShape kDownRegs = {64, 128, 3.8, 0.24, 0.04};
 // Tile shape and K splits (up to the partials the workspace holds): the least of
 // start-up + loops + the partials' reduction (a launch, and writing and reading
 // them). 64-row tiles take their weights into registers wherever that kernel fits
-// one round (at M = 65..1024 it was the faster one at every split, by 0.4 to 4 us
-// of the whole FFN). The constants are fitted to the whole FFN call at 188 sizes, M =
+// one round (at M = 65..1024 and every split it was up to 4 us faster of the whole
+// FFN, nowhere slower beyond noise). The constants are fitted to the whole FFN call at 188 sizes, M =
 // 65..8192, H = 128..16384, I = 1024..16384, all shapes and splits in turn in one
 // process; the chosen one is on average 0.13 % slower than the best, 4.8 % at most.
 // 128 x 256 tiles over the workspace's splits stay unless another choice is more
