@@ -564,7 +564,8 @@ hipError_t launch_gateup_skinny(hipStream_t st, const uint8_t* xq, const float* 
   }
   // the ring of a workgroup of fewer wavefronts is deeper, up to a part's K-groups
   // (steps past them multiply by zero scales: at H = 2048, I = 4096, 32 rows the
-  // call takes 20.7 us with a ring of 6, 19.1 with 4)
+  // call takes 20.7 us with a ring of 6, 19.1 with 4; H = 2560, I = 4096, 48 rows:
+  // 26.2 with a ring of 8, 25.4 with 4)
   const int64_t nkw = (H / 128 + 3) / 4;
   if (!one) {
     if (mt == 3)
@@ -581,10 +582,12 @@ hipError_t launch_gateup_skinny(hipStream_t st, const uint8_t* xq, const float* 
     }
   } else if (pairs == 2) {
     SG1(2, 4)
-  } else if (nkw <= 4) {
+  } else if (nkw <= 4 || mt > 2) {  // (33..64 rows in one piece: at most 6 K-groups)
     SG1(1, 4)
+  } else if (mt == 1) {
+    SG(1, 1, 1, 8);
   } else {
-    SG1(1, 8)
+    SG(2, 1, 1, 8);
   }
 #undef SG1
 #undef SG
