@@ -432,12 +432,12 @@ def test_skinny_k_parts(M, H, I):
 
 
 @pytest.mark.parametrize("M,H,I", [(5, 384, 4224), (48, 2560, 4224), (20, 256, 8320), (33, 128, 8192),
-                                   (64, 2048, 128), (64, 2176, 256)])
+                                   (64, 2048, 128), (64, 2176, 256), (48, 2688, 128)])
 def test_skinny_slab_pairs_per_workgroup(M, H, I):
     """The gate/up kernel's other workgroup shapes: 2 slab pairs x 4 K parts
     (I = 4224, 8192), 3 x 4 with a partial last workgroup (I = 8320) and 1 x
     4 (I = 128, 256), at 33..64 rows with all of K in the LDS up to its
-    largest (H = 2560 at 48 rows, 2048 at 64) and with two K halves just above
+    largest (H = 2688 at 48 rows, 2048 at 64) and with two K halves just above
     (2176 at 64)."""
     _say("skinny pairs M=%d H=%d I=%d" % (M, H, I))
     lc.lacache_set_path_policy(1)
